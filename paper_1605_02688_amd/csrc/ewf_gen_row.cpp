@@ -208,21 +208,24 @@ ewf_status Gen::gen_row()
     const bool ragged = loose && cols % VEC != 0;
     const std::string whole = "(u < " + std::to_string(NFULL) + " || col + EWF_VEC <= cols)";
     const std::string inside = ragged ? "if (u < " + std::to_string(NFULL) + " || col + e_ < cols) " : std::string("");
+    const std::string cut_len = std::to_string(cols % VEC);
+    auto streamed = [](const Operand &op) { return op.stream ? ", ewf_streamed()" : ""; };
     auto emit_row_load = [&](int k, const std::string &ind, const std::string &dst) {
         const Operand &op = c.ops[k];
         std::string nm = opname(k);
         if (op.access == Access::Vector && loose) {
             if (ragged) {
-                o << ind << "if " << whole << " " << dst << " = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col);\n";
-                o << ind << "else { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC - 1; ++e_) if (col + e_ < cols) " << dst << ".e[e_] = q_" << nm << "[col + e_]; }\n";
+                o << ind << "if (u < " << NFULL << ") " << dst << " = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col" << streamed(op) << ");\n";
+                o << ind << "else " << dst << " = ewf_ld_cut<" << ctype(op.storage) << ", EWF_VEC, " << cut_len << ">(q_" << nm << " + col, col + EWF_VEC > cols);\n";
             }
-            else o << ind << dst << " = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col);\n";
+            else o << ind << dst << " = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col" << streamed(op) << ");\n";
         }
         else if (op.access == Access::Vector)
             o << ind << dst << " = " << (op.stream ? "ewf_ld_nt<" : "ewf_ld<") << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col);\n";
         else
-            o << ind << "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) " << inside << dst << ".e[e_] = q_" << nm
-              << "[(col + e_) * p.st_" << nm << "[" << in_d << "]];\n";
+            o << ind << "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) " << dst << ".e[e_] = q_" << nm
+              << "[" << (ragged ? "(u < " + std::to_string(NFULL) + " || col + e_ < cols ? col + e_ : cols - 1)" : std::string("(col + e_)"))
+              << " * p.st_" << nm << "[" << in_d << "]];\n";
     };
 
     // values constant along the row come first: an index that a gather depends on is then
@@ -238,9 +241,37 @@ ewf_status Gen::gen_row()
     }
     if (resident) {
         for (int k : row_ops) if (!late[k]) o << "        ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> x_" << opname(k) << "[" << U << "];\n";
-        open_pass();
-        for (int k : row_ops) if (!late[k]) emit_row_load(k, "            ", "x_" + opname(k) + "[u]");
-        close_pass();
+        if (NFULL > 0 || !ragged) {
+            if (ragged) {
+                // the whole steps here; the last one below, where the cut vector is moved into
+                // place behind all the loads
+                o << "        #pragma unroll\n        for (int u = 0; u < " << NFULL << "; ++u) {\n";
+                o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + tid) * EWF_VEC;\n";
+            }
+            else open_pass();
+            for (int k : row_ops) if (!late[k]) emit_row_load(k, "            ", "x_" + opname(k) + "[u]");
+            close_pass();
+        }
+        if (ragged) {
+            o << "        #pragma unroll\n        for (int u = " << NFULL << "; u < " << U << "; ++u) {\n";
+            o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + tid) * EWF_VEC;\n";
+            o << "            const idx_t at_ = col + EWF_VEC <= cols ? col : cols - EWF_VEC;\n";
+            o << "            if (col < cols) {\n";
+            for (int k : row_ops) {
+                if (late[k]) continue;
+                if (c.ops[k].access == Access::Vector)
+                    o << "                x_" << opname(k) << "[u] = ewf_ld_u<" << ctype(c.ops[k].storage) << ", EWF_VEC>(q_" << opname(k) << " + at_" << streamed(c.ops[k]) << ");\n";
+                else
+                    emit_row_load(k, "                ", "x_" + opname(k) + "[u]");
+            }
+            o << "            }\n";
+            o << "        }\n        #pragma unroll\n        for (int u = " << NFULL << "; u < " << U << "; ++u) {\n";
+            o << "            const bool cut_ = (idx_t)(u * EWF_BLOCK + tid) * EWF_VEC + EWF_VEC > cols;\n";
+            for (int k : row_ops)
+                if (!late[k] && c.ops[k].access == Access::Vector)
+                    o << "            x_" << opname(k) << "[u] = ewf_move_cut<" << ctype(c.ops[k].storage) << ", EWF_VEC, " << cut_len << ">(x_" << opname(k) << "[u], cut_);\n";
+            o << "        }\n";
+        }
     }
 
     EmitCtx cx;
@@ -372,7 +403,6 @@ ewf_status Gen::gen_row()
         stream_loads(need);
         for (int k : full_out_ops) o << "            ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> y_" << opname(k) << ";\n";
         o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
-        if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
         emit_values(need, cx, "                ");
         for (int k : full_out_ops) {
             const Operand &op = c.ops[k];
@@ -385,10 +415,10 @@ ewf_status Gen::gen_row()
             std::string nm = opname(k);
             if (op.access == Access::Vector && loose) {
                 if (ragged) {
-                    o << "            if " << whole << " ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << ");\n";
-                    o << "            else { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC - 1; ++e_) if (col + e_ < cols) q_" << nm << "[col + e_] = y_" << nm << ".e[e_]; }\n";
+                    o << "            if " << whole << " ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << streamed(op) << ");\n";
+                    o << "            else ewf_st_cut<" << ctype(op.storage) << ", EWF_VEC, " << cut_len << ">(q_" << nm << " + col, y_" << nm << ");\n";
                 }
-                else o << "            ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << ");\n";
+                else o << "            ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << streamed(op) << ");\n";
             }
             else if (op.access == Access::Vector)
                 o << "            " << (op.stream ? "ewf_st_nt<" : "ewf_st<") << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << ");\n";

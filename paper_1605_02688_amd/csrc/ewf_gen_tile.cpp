@@ -61,6 +61,13 @@ ewf_status Gen::gen_tile(bool with_reduce)
     // last vector handled element by element (`ragged`).
     const bool loose = p.loose_vec;
     const bool ragged = loose && c.extent[R - 1] % VEC != 0;
+    auto streamed = [](const Operand &op) { return op.stream ? ", ewf_streamed()" : ""; };
+    const std::string cut_len = std::to_string(c.extent[R - 1] % VEC);      // elements of the vector that a row's end cuts
+    // A cut vector is read as the row's last whole vector and moved into place (ewf_move_cut); only
+    // the float32 operands of a reducing kernel keep the element-by-element reads, which wait for
+    // nothing there (the backward pass of bias + ReLU + channel sums on float32 [8, 1349, 77, 77]
+    // 139.6 against 141.5 us with the move).
+    auto moves_cut = [&](const Operand &op) { return !with_reduce || isz(op.storage) == 2; };
     // ---- tile shape: innermost dimensions first, never across a group boundary
     int64_t T[kMaxDims];
     for (int d = 0; d < kMaxDims; d++) T[d] = 1;
@@ -580,11 +587,14 @@ ewf_status Gen::gen_tile(bool with_reduce)
             }
             else if (op.access == Access::Vector && loose) {
                 o << ind << "        { const " << ctype(op.storage) << " *const a_ = ewf_at(q_" << nm << ", " << offset_expr(k, false) << ");\n";
-                if (ragged) {
-                    o << ind << "          if (it.nv[u] == EWF_VEC) it.x_" << nm << "[u] = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(a_);\n";
+                if (ragged && !moves_cut(op)) {
+                    o << ind << "          if (it.nv[u] == EWF_VEC) it.x_" << nm << "[u] = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(a_" << streamed(op) << ");\n";
                     o << ind << "          else { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC - 1; ++e_) if (e_ < it.nv[u]) it.x_" << nm << "[u].e[e_] = a_[e_]; } }\n";
                 }
-                else o << ind << "          it.x_" << nm << "[u] = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(a_); }\n";
+                else if (ragged) {
+                    o << ind << "          it.x_" << nm << "[u] = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(a_ - (it.nv[u] != EWF_VEC ? EWF_VEC - " << cut_len << " : 0)" << streamed(op) << "); }\n";
+                }
+                else o << ind << "          it.x_" << nm << "[u] = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(a_" << streamed(op) << "); }\n";
             }
             else if (op.access == Access::Vector)
                 o << ind << "        it.x_" << nm << "[u] = " << (op.stream ? "ewf_ld_nt<" : "ewf_ld<") << ctype(op.storage) << ", EWF_VEC>(ewf_at(q_" << nm << ", " << offset_expr(k, false) << "));\n";
@@ -592,13 +602,19 @@ ewf_status Gen::gen_tile(bool with_reduce)
                 o << ind << "        it.x_" << nm << "[u] = *ewf_at(q_" << nm << ", " << offset_expr(k, true) << ");\n";
             else {
                 o << ind << "        { const ioff_t b_ = " << offset_expr(k, false) << ";\n";
-                o << ind << "          _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) " << (ragged ? "if (e_ < it.nv[u]) " : "") << "it.x_" << nm << "[u].e[e_] = *ewf_at(q_" << nm
-                  << ", b_ + (ioff_t)e_ * (ioff_t)p.st_" << nm << "[" << in_d << "]); }\n";
+                // (past the end of a cut vector the row's last element is read again: no branch per element)
+                o << ind << "          _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) it.x_" << nm << "[u].e[e_] = *ewf_at(q_" << nm
+                  << ", b_ + (ioff_t)" << (ragged ? "(e_ < it.nv[u] ? e_ : it.nv[u] - 1)" : "e_") << " * (ioff_t)p.st_" << nm << "[" << in_d << "]); }\n";
             }
         }
     });
     const std::string text_c = capture([&]() {
         const std::string &ind = ind2;
+        // (moved here rather than behind its load, so that no load waits for the one before)
+        if (ragged)
+            for (int k : load_ops)
+                if (c.ops[k].access == Access::Vector && !is_staged(k) && moves_cut(c.ops[k]))
+                    o << ind << "    if (it.nv[u] != EWF_VEC) it.x_" << opname(k) << "[u] = ewf_move_cut<" << ctype(c.ops[k].storage) << ", EWF_VEC, " << cut_len << ">(it.x_" << opname(k) << "[u], true);\n";
         for (int k : ew_out_ops) o << ind << "    ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> y_" << opname(k) << ";\n";
         // slots that take a vector of elements at once keep the element loop's values of their
         // argument and are folded after it
@@ -628,7 +644,8 @@ ewf_status Gen::gen_tile(bool with_reduce)
             if (d == in_d) s += " + e_";
             return s;
         };
-        if (ragged) o << ind << "        if (e_ >= it.nv[u]) continue;\n";
+        // (an element-wise kernel evaluates all of a cut vector and stores the part inside the row)
+        if (ragged && with_reduce) o << ind << "        if (e_ >= it.nv[u]) continue;\n";
         emit_values(need, cx, ind + "        ");
         if (with_reduce)
             emit_accumulate("acc", level, [&](int node) { return argmax_index(node, cx.coord); }, ind + "        ", ascending, &eslots);
@@ -649,10 +666,10 @@ ewf_status Gen::gen_tile(bool with_reduce)
             if (op.access == Access::Vector && loose) {
                 o << ind << "    { " << ctype(op.storage) << " *const a_ = ewf_at(q_" << nm << ", " << offset_expr(k, false) << ");\n";
                 if (ragged) {
-                    o << ind << "      if (it.nv[u] == EWF_VEC) ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(a_, y_" << nm << ");\n";
-                    o << ind << "      else { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC - 1; ++e_) if (e_ < it.nv[u]) a_[e_] = y_" << nm << ".e[e_]; } }\n";
+                    o << ind << "      if (it.nv[u] == EWF_VEC) ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(a_, y_" << nm << streamed(op) << ");\n";
+                    o << ind << "      else ewf_st_cut<" << ctype(op.storage) << ", EWF_VEC, " << cut_len << ">(a_, y_" << nm << "); }\n";
                 }
-                else o << ind << "      ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(a_, y_" << nm << "); }\n";
+                else o << ind << "      ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(a_, y_" << nm << streamed(op) << "); }\n";
             }
             else if (op.access == Access::Vector)
                 o << ind << "    " << (op.stream ? "ewf_st_nt<" : "ewf_st<") << ctype(op.storage) << ", EWF_VEC>(ewf_at(q_" << nm << ", " << offset_expr(k, false) << "), y_" << nm << ");\n";
@@ -671,7 +688,7 @@ ewf_status Gen::gen_tile(bool with_reduce)
         o << ind2 << "    it.ok[u] = k_;\n";
         o << ind2 << "    if (k_) {\n" << text_b << ind2 << "    }\n" << ind2 << "}\n";
         o << ind << "};\n";
-        o << ind << "auto eval_item = [&](const Item &it) {\n";
+        o << ind << "auto eval_item = [&](Item &it) {\n";
         o << ind2 << "#pragma unroll\n" << ind2 << "for (int u = 0; u < " << U << "; ++u) {\n";
         o << ind2 << "    if (!it.ok[u]) continue;\n";
         o << text_c;
