@@ -76,6 +76,20 @@ void finish_layout(ParamLayout &L)
 
 // =========================================================================================
 
+// Roughly the vector instructions an operation takes per element (the native-rate flavours; a
+// transcendental instruction occupies two or more issue slots).
+static double instructions_of(const Node &n)
+{
+    if (n.kind == NodeKind::Cast || n.kind == NodeKind::Input) return 1;
+    if (n.kind != NodeKind::Apply) return 0;
+    switch (n.op) {
+    case EWF_EXP: case EWF_LOG: case EWF_LOG1P: case EWF_EXPM1: return 4;
+    case EWF_POW: case EWF_TANH: case EWF_SIGMOID: return 6;
+    case EWF_DIV: case EWF_RECIP: case EWF_SQRT: case EWF_WHERE: return 2;
+    default: return 1;
+    }
+}
+
 ewf_status generate(const Exec &e, Plan &p)
 {
     // The tile and row classes can use wide accesses on rows that start at any element and end inside a
@@ -94,7 +108,7 @@ ewf_status generate(const Exec &e, Plan &p)
     int narrowest = 4;
     for (const Operand &op : c.ops) if (op.stride[c.rank - 1] != 0) narrowest = std::min(narrowest, op.storage == EWF_F16 ? 2 : 4);
     const bool worth = p.kclass == KernelClass::TileReduce || p.kclass == KernelClass::Row ||
-                       (p.kclass == KernelClass::Tile && c.vec * narrowest <= 2);
+                       (p.kclass == KernelClass::Tile && c.vec * narrowest <= 2 && Gen(e, p).permuted_operand() < 0);
     if (worth && c.vec_loose > c.vec && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
         const int strict = c.vec;
         p.canon.vec = c.vec_loose;
@@ -104,6 +118,32 @@ ewf_status generate(const Exec &e, Plan &p)
         if (st == EWF_OK) return st;
         p.canon.vec = strict;
         p.loose_vec = false;
+    }
+    // Element-wise kernels that stage a permuted operand through LDS: rows that allow only narrow
+    // accesses are read, evaluated and written in wider vectors too.  A row's last vector then
+    // works on elements past the row's end, so the width is the one that costs the fewest
+    // instructions: a vector costs its address arithmetic and accesses whatever it holds, an
+    // element the expression.
+    if (p.kclass == KernelClass::Tile && c.vec_loose > c.vec && !e.opts.force_scalar && !e.opts.no_lds_staging) {
+        const Gen probe(e, p);
+        if (probe.permuted_operand() >= 0) {
+            const int strict = c.vec;
+            const int64_t row = c.extent[c.rank - 1];
+            double per_element = 4, per_vector = 30;
+            for (size_t n = 0; n < e.g.nodes.size(); n++) if (probe.live[n]) per_element += instructions_of(e.g.nodes[n]);
+            for (size_t k = 0; k < c.ops.size(); k++) per_vector += 6;
+            auto cost = [&](int v) { return (double)((row + v - 1) / v) * (per_vector + per_element * v); };
+            int best = strict;
+            for (int v = 2 * strict; v <= c.vec_loose && v <= row; v *= 2) if (cost(v) < (best == strict ? 0.95 : 1.0) * cost(best)) best = v;
+            if (best > strict) {
+                p.canon.vec = best;
+                p.loose_vec = true;
+                Gen wide(e, p);
+                if (wide.gen_tile(false) == EWF_OK) return EWF_OK;
+                p.canon.vec = strict;
+                p.loose_vec = false;
+            }
+        }
     }
     Gen gen(e, p);
     switch (p.kclass) {

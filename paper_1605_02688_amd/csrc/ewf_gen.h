@@ -576,6 +576,23 @@ struct Gen {
     // of range).  The row class reads that element directly instead of comparing an index
     // per element.  Adding +0 keeps the sign rule of the sum (a sum of zeros is +0).
     struct Gather { int node, input, index_value, cdim; };
+    // An operand that an element-wise kernel would read against its own memory order (its
+    // unit-stride dimension is not the innermost one): the first one that is worth staging through
+    // LDS, or -1.
+    int permuted_operand() const
+    {
+        if (c.total < 65536 || R < 2) return -1;
+        for (int k = 0; k < g.ninputs; k++) {
+            const Operand &op = c.ops[k];
+            if (op.access != Access::Gather || !live[g.input_node[k]]) continue;      // (an input no output uses is never read)
+            bool full = true;
+            int s0 = -1;
+            for (int d = 0; d < R; d++) { if (op.stride[d] == 0) full = false; if (op.stride[d] == 1) s0 = d; }
+            if (full && s0 >= 0 && c.extent[s0] >= 16) return k;
+        }
+        return -1;
+    }
+
     bool match_gather(int n, Gather &out) const
     {
         const Node &nd = g.nodes[n];

@@ -209,7 +209,7 @@ ewf_status Gen::gen_row()
     const std::string whole = "(u < " + std::to_string(NFULL) + " || col + EWF_VEC <= cols)";
     const std::string inside = ragged ? "if (u < " + std::to_string(NFULL) + " || col + e_ < cols) " : std::string("");
     const std::string cut_len = std::to_string(cols % VEC);
-    auto streamed = [](const Operand &op) { return op.stream ? ", ewf_streamed()" : ""; };
+    auto streamed = [&](const Operand &op) { return op.stream && VEC * isz(op.storage) % 16 == 0 ? ", ewf_streamed()" : ""; };
     auto emit_row_load = [&](int k, const std::string &ind, const std::string &dst) {
         const Operand &op = c.ops[k];
         std::string nm = opname(k);

@@ -61,7 +61,7 @@ ewf_status Gen::gen_tile(bool with_reduce)
     // last vector handled element by element (`ragged`).
     const bool loose = p.loose_vec;
     const bool ragged = loose && c.extent[R - 1] % VEC != 0;
-    auto streamed = [](const Operand &op) { return op.stream ? ", ewf_streamed()" : ""; };
+    auto streamed = [&](const Operand &op) { return op.stream && VEC * isz(op.storage) % 16 == 0 ? ", ewf_streamed()" : ""; };
     const std::string cut_len = std::to_string(c.extent[R - 1] % VEC);      // elements of the vector that a row's end cuts
     // A cut vector is read as the row's last whole vector and moved into place (ewf_move_cut); only
     // the float32 operands of a reducing kernel keep the element-by-element reads, which wait for
@@ -148,16 +148,12 @@ ewf_status Gen::gen_tile(bool with_reduce)
     std::vector<int> staged;                           // operand numbers
     std::vector<int> sdims;                            // dims ordered by the staged operand's stride
     int VS = 1;
-    if (!with_reduce && !e.opts.no_lds_staging && c.total >= 65536 && R >= 2 && !loose) {
-        for (int k = 0; k < nin && staged.empty(); k++) {
-            const Operand &op = c.ops[k];
-            if (op.access != Access::Gather || !live[g.input_node[k]]) continue;      // (an input no output uses is never read)
-            bool full = true; int s0 = -1;
-            for (int d = 0; d < R; d++) { if (op.stride[d] == 0) full = false; if (op.stride[d] == 1) s0 = d; }
-            if (!full || s0 < 0 || c.extent[s0] < 16) continue;
-            staged.push_back(k);
-        }
+    if (!with_reduce && !e.opts.no_lds_staging) {
+        const int k = permuted_operand();
+        if (k >= 0) staged.push_back(k);
     }
+    int64_t ST[kMaxDims];                              // the part of the tile that is staged: without the tile's padding, pieces whole
+    bool stage_loose = false;                          // pieces that assume element alignment only, the last of a run moved back to end with it
     if (!staged.empty()) {
         const Operand &S = c.ops[staged[0]];
         const int szS = isz(S.storage);
@@ -171,14 +167,37 @@ ewf_status Gen::gen_tile(bool with_reduce)
             if (same) staged.push_back(k);
         }
         // 64 KiB of LDS per staged operand (two workgroups per compute unit): room for runs along
-        // the output's order that are whole cache lines
-        const int64_t budget = (e.opts.tile_elems > 0 ? e.opts.tile_elems : 65536 / szS);
+        // the output's order that are whole cache lines.  But no fewer than about four tiles per
+        // compute unit while a tile still holds 2048 elements: a small tensor is otherwise a
+        // handful of workgroups (the stress expression on float16 [1, 34, 77, 36] in five tiles
+        // 44.6 us, in 80 3.3 us; [43, 96, 27, 72] in 344 tiles 28.6, in 1032 19.5 us).  With
+        // little arithmetic to spread, full tiles for half the compute units stream as well or
+        // better (x + y^T on float32 [64, 100000] in 392 tiles 16.3 us, in 1042 19.2 us; [8, 512, 512] in
+        // 128 6.0, in 512 6.8 us; but [1024, 1024] in 64 5.3, in 512 4.1 us).
+        const int64_t full_tile = 65536 / szS;
+        const int64_t budget = e.opts.tile_elems > 0 ? e.opts.tile_elems
+                               : heavy < 4 && c.total >= device_cu_count() / 2 * full_tile ? full_tile
+                               : std::min(full_tile, std::max<int64_t>(2048, c.total / ((int64_t)4 * device_cu_count())));
         for (int d = 0; d < kMaxDims; d++) T[d] = 1;
-        // runs of at least 128 bytes along the staged operand's memory order
-        int64_t need_run = 128 / szS;
+        // Runs of at least 128 bytes along the staged operand's memory order; 64 where the tile's
+        // runs along the output's order cannot be whole lines (see shares_lines): the dies then
+        // share lines on both sides, and longer runs of the operands that are not staged, of
+        // which there are more, count for more (reading "A" of the float16 stress workload,
+        // [43, 96, 27, 72] 23.6 -> 19.6 us, [48, 160, 14, 14] 7.7 -> 6.6 us; planes of 56 x 56, whole
+        // lines, 89.8 -> 115.8 us).
+        int64_t plane = 1;
+        for (int d = R - 1; d > sdims[0]; d--) plane *= c.extent[d];
+        const bool split_lines = plane * szS >= 512 && plane * szS <= 8192 && (plane * szS % 128 != 0 || budget < 65536 / szS);
+        int64_t need_run = (split_lines ? 64 : 128) / szS;
         for (size_t i = 0; i < sdims.size() && need_run > 1; i++) {
             int d = sdims[i];
             T[d] = std::min<int64_t>(c.extent[d], need_run);
+            if (T[d] < c.extent[d] && c.extent[d] % T[d]) {
+                // even shares: 97 channels as 33 + 33 + 31, not 32 + 32 + 32 + 1 (whole pieces where
+                // the extent is made of them)
+                const int64_t n = std::max<int64_t>(1, (c.extent[d] + T[d] / 2) / T[d]), whole = c.extent[d] % (16 / szS) == 0 ? 16 / szS : 1;
+                T[d] = std::min(c.extent[d], ceil_div(ceil_div(c.extent[d], n), whole) * whole);
+            }
             if (T[d] < c.extent[d]) break;
             if (i + 1 < sdims.size() && S.stride[sdims[i + 1]] != S.stride[d] * c.extent[d]) break;
             need_run = ceil_div(need_run, T[d]);
@@ -188,6 +207,9 @@ ewf_status Gen::gen_tile(bool with_reduce)
             int64_t others = 1;
             for (int d2 = 0; d2 < R; d2++) if (d2 != d) others *= T[d2];
             int64_t cap = std::max<int64_t>(1, budget / others);
+            // (a row that is a little longer than a small tile's share is taken whole rather than
+            // in two tiles, the second nearly empty)
+            if (d == R - 1 && e.opts.tile_elems <= 0 && c.extent[d] > cap && c.extent[d] * 2 <= cap * 3 && others * (c.extent[d] + VEC) * szS <= 65536) cap = c.extent[d] + VEC;
             int64_t t = std::max<int64_t>(T[d], std::min<int64_t>(c.extent[d], cap));
             if (t < c.extent[d]) {
                 // prefer a split whose runs in the contiguous operands are whole 128-byte lines
@@ -202,9 +224,14 @@ ewf_status Gen::gen_tile(bool with_reduce)
                 }
                 t = best_q;
             }
-            if (d == R - 1) t = std::max<int64_t>(VEC, t / VEC * VEC);
+            bool whole_dim = t >= c.extent[d];
+            if (d == R - 1) {
+                const int64_t padded = ceil_div(t, VEC) * VEC;
+                if (padded * 2 > cap * 3 && t > T[d]) whole_dim = false;
+                t = std::max<int64_t>(VEC, loose && whole_dim ? padded : t / VEC * VEC);
+            }
             T[d] = t;
-            if (t < c.extent[d]) break;
+            if (!whole_dim) break;
         }
         // vector width on the staging side
         const int s0 = sdims[0];
@@ -218,7 +245,31 @@ ewf_status Gen::gen_tile(bool with_reduce)
             return true;
         };
         while (VS > 1 && !vs_ok(VS)) VS /= 2;
+        for (int d = 0; d < R; d++) ST[d] = std::min(T[d], c.extent[d]);
+        // Runs that allow only narrow pieces (an odd extent, an odd pitch) are read wide all the same:
+        // the memory instructions take any address, and the last piece of a run is moved back so
+        // that it ends with the run; what it shares with the piece before is written to LDS twice.
+        // (Pieces of eight bytes are wide enough: x + y^T on float16 [100000, 64], runs of 500, 9.6 us
+        // with them and 10.9 us with moved pieces of sixteen.)
+        if (VS * szS < 8) {
+            const int64_t last = c.extent[s0] % T[s0] ? c.extent[s0] % T[s0] : ST[s0];       // the run in the last tile
+            int best = VS;
+            auto cost = [&](int v) { return ceil_div(ST[s0], v) * (v + 4); };                // LDS writes and the index arithmetic of a piece
+            for (int v = 2 * VS; v * szS <= 16; v *= 2)
+                if (v <= last && cost(v) < cost(best)) best = v;
+            if (best != VS) { VS = best; stage_loose = true; }
+        }
+        ST[s0] = ceil_div(ST[s0], VS) * VS;
     }
+    bool shares_lines = false;                         // the staged tile's runs along the output's order start or end inside 128-byte lines
+    if (!staged.empty()) {
+        int64_t inside = isz(c.ops[staged[0]].storage);          // bytes of the dimensions the tile holds whole
+        int d = R - 1;
+        while (d > 0 && T[d] >= c.extent[d]) inside *= c.extent[d--];
+        shares_lines = inside * T[d] <= 4096 && (inside * T[d] % 128 != 0 || inside * c.extent[d] % 128 != 0);
+    }
+    int64_t SE = 1;
+    if (!staged.empty()) for (int d = 0; d < R; d++) SE *= ST[d];
     auto is_staged = [&](int k) { return std::find(staged.begin(), staged.end(), k) != staged.end(); };
     if (!staged.empty() && e.opts.block_threads <= 0) {
         // two workgroups of twelve wavefronts share a compute unit when the staged tile takes about
@@ -234,6 +285,9 @@ ewf_status Gen::gen_tile(bool with_reduce)
             // 91.7-93.0 us, 512 threads with the two last trips in one 89.7-90.0 us)
             auto last_fill = [&](int64_t b) { const int64_t s_ = b * VEC * U, n_ = ceil_div(te, s_); return (double)(te - (n_ - 1) * s_) / (double)s_; };
             if (e.opts.no_prefetch != 1 && last_fill(768) <= 0.25 && last_fill(512) <= 0.25) block = 512;
+        } else {
+            // smaller tiles: four wavefronts, eight where they would take more than three trips
+            block = te > (int64_t)256 * VEC * U * 3 ? 512 : 256;
         }
     }
     p.block = block;
@@ -248,7 +302,7 @@ ewf_status Gen::gen_tile(bool with_reduce)
         const int s0 = sdims[0];
         const int szS = isz(c.ops[staged[0]].storage);
         std::vector<int> st;
-        for (int d : sdims) if (T[d] > 1) st.push_back(d);
+        for (int d : sdims) if (ST[d] > 1) st.push_back(d);
         // Which 16-byte piece of the staged tile a lane loads.  Taken in the operand's memory
         // order, the 64 lanes of a wavefront may differ only along dimensions that are slow in the
         // LDS copy, and their scattered writes then fall into a few banks whatever the padding
@@ -262,9 +316,9 @@ ewf_status Gen::gen_tile(bool with_reduce)
             const int pd = R - 1;
             auto at = std::find(st.begin(), st.end(), pd);
             int64_t A = 1;
-            for (int d : st) if (d != pd) A *= T[d];
+            for (int d : st) if (d != pd) A *= ST[d];
             A /= VS;
-            if (at != st.end() && pd != s0 && st.size() >= 2 && A % 8 == 0 && T[pd] % 8 == 0) {
+            if (at != st.end() && pd != s0 && st.size() >= 2 && A % 8 == 0 && ST[pd] % 8 == 0) {
                 st.erase(at);
                 st.push_back(pd);
                 stage_patch_a = A;
@@ -287,7 +341,7 @@ ewf_status Gen::gen_tile(bool with_reduce)
                     int64_t j = piece_of(lane) * VS, addr = 0;
                     for (size_t i = 0; i < st.size(); i++) {
                         int d = st[i];
-                        int64_t cd = (i + 1 < st.size()) ? j % T[d] : j; j /= T[d];
+                        int64_t cd = (i + 1 < st.size()) ? j % ST[d] : j; j /= ST[d];
                         int64_t ls = LS[d];
                         if (LS[d] >= LS[s0]) ls = LS[d] / LS[s0] * (LS[s0] + pad);
                         addr += cd * ls;
@@ -412,7 +466,10 @@ ewf_status Gen::gen_tile(bool with_reduce)
     // (w mod 8) * ceil(ntiles / 8) + w / 8, so the tiles in flight on one die are neighbours
     // in memory.  Off by default: measured slower on the streaming workloads (eight distant
     // streams instead of one; 145 us against 136 us on the bias + ReLU + channel-sum workload).
-    const bool xcd_remap = e.opts.xcd_remap && ntiles >= 64;
+    // On for staged tiles whose runs are not whole 128-byte lines: neighbouring tiles then share
+    // lines, which one die's L2 holds for both (reading "A" of the float16 stress workload, [48, 160, 14, 14]
+    // 9.9 -> 7.7 us, [43, 96, 27, 72] 27.2 -> 23.6 us; whole lines, [64, 256, 56, 56] 89.8 -> 94.4 us).
+    const bool xcd_remap = (e.opts.xcd_remap || shares_lines) && ntiles >= 64;
     if (xcd_remap) {
         o << "    const idx_t chunk_ = (p.ntiles + 7) / 8;\n";
         o << "    for (idx_t wg_ = blockIdx.x; wg_ < chunk_ * 8; wg_ += gridDim.x) {\n";
@@ -451,9 +508,9 @@ ewf_status Gen::gen_tile(bool with_reduce)
         // piece outside the tile reads the tile's first piece instead), then the scattered LDS
         // writes of the pieces inside.  (With a branch around each load the trips ran one after
         // the other, a round trip to memory each: 5 % on the float16 stress workload.)
-        const int64_t trips_ = ceil_div(TE, (int64_t)block * VS);
+        const int64_t trips_ = ceil_div(SE, (int64_t)block * VS);
         const int64_t chunk_ = std::min<int64_t>(trips_, 8);
-        o << ind << "for (int J00 = 0; J00 < " << TE << "; J00 += " << chunk_ * block * VS << ") {\n";
+        o << ind << "for (int J00 = 0; J00 < " << SE << "; J00 += " << chunk_ * block * VS << ") {\n";
         o << ind << "    int slm_[" << chunk_ << "]; bool sk_[" << chunk_ << "];\n";
         for (int k : staged) o << ind << "    ewf_vec<" << ctype(c.ops[k].storage) << ", " << VS << "> sv_" << opname(k) << "[" << chunk_ << "];\n";
         o << ind << "    _Pragma(\"unroll\") for (int t_ = 0; t_ < " << chunk_ << "; ++t_) {\n";
@@ -467,16 +524,20 @@ ewf_status Gen::gen_tile(bool with_reduce)
         } else {
             o << ind << "    int j_ = J0 + tid * " << VS << ";\n";
         }
-        o << ind << "    bool k_ = J0 < " << TE << " && j_ < " << TE << ";\n";
+        o << ind << "    bool k_ = J0 < " << SE << " && j_ < " << SE << ";\n";
         o << ind << "    int lm_ = 0; ioff_t g_ = 0;\n";
         const std::vector<int> &st = stage_order;      // the staged operand's dims with T > 1, fastest digit first
-        int64_t jrange = TE;                           // what is left of j_ stays below this (for pieces inside the tile)
+        int64_t jrange = SE;                           // what is left of j_ stays below this (for pieces inside the tile)
         for (size_t i = 0; i < st.size(); i++) {
             int d = st[i];
-            if (i + 1 < st.size()) o << ind << "    { int c_; " << divmod_small("c_", "j_", T[d], jrange) << "\n";
-            else o << ind << "    { const int c_ = j_;\n";
-            jrange = ceil_div(jrange, T[d]);
-            if (c.extent[d] % T[d]) o << ind << "      k_ = k_ && (o" << d << " + c_ < p.ext[" << d << "]);\n";
+            if (i + 1 < st.size()) o << ind << "    { int c_; " << divmod_small("c_", "j_", ST[d], jrange) << "\n";
+            else o << ind << "    { int c_ = j_;\n";
+            jrange = ceil_div(jrange, ST[d]);
+            if (c.extent[d] % T[d] && T[d] < c.extent[d]) o << ind << "      k_ = k_ && (o" << d << " + c_ < p.ext[" << d << "]);\n";
+            if (d == s0 && stage_loose) {
+                if (c.extent[d] % T[d] && T[d] < c.extent[d]) o << ind << "      { const int end_ = (int)(p.ext[" << d << "] - o" << d << "); const int lim_ = (end_ < " << T[d] << " ? end_ : " << T[d] << ") - " << VS << "; if (c_ > lim_) c_ = lim_; }\n";
+                else o << ind << "      if (c_ > " << std::min(T[d], c.extent[d]) - VS << ") c_ = " << std::min(T[d], c.extent[d]) - VS << ";\n";
+            }
             o << ind << "      lm_ += c_ * " << LSP[d] << ";\n";
             if (d == s0) o << ind << "      g_ += (ioff_t)c_; }\n";
             else o << ind << "      g_ += " << product("c_", "p.st_" + opname(staged[0]) + "[" + std::to_string(d) + "]", c.ops[staged[0]].stride[d]) << "; }\n";
@@ -490,7 +551,8 @@ ewf_status Gen::gen_tile(bool with_reduce)
             int64_t fp_ = isz(op.storage);
             for (int d = 0; d < R; d++) if (op.stride[d] != 0) fp_ *= c.extent[d];
             const bool nt_ = e.opts.streaming == 1 || (e.opts.streaming == 0 && fp_ >= ((int64_t)32 << 20));
-            o << ind << "    sv_" << opname(k) << "[t_] = " << (nt_ ? "ewf_ld_nt<" : "ewf_ld<") << ctype(op.storage) << ", " << VS << ">(ewf_at(q_" << opname(k) << ", g_));\n";
+            o << ind << "    sv_" << opname(k) << "[t_] = " << (stage_loose ? "ewf_ld_u<" : nt_ ? "ewf_ld_nt<" : "ewf_ld<") << ctype(op.storage) << ", " << VS << ">(ewf_at(q_" << opname(k) << ", g_)"
+              << (stage_loose && nt_ && VS * isz(op.storage) == 16 ? ", ewf_streamed()" : "") << ");\n";
         }
         o << ind << "    }\n";
         o << ind << "    _Pragma(\"unroll\") for (int t_ = 0; t_ < " << chunk_ << "; ++t_) {\n";
