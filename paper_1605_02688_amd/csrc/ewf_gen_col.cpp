@@ -39,18 +39,57 @@ ewf_status Gen::gen_col()
     int TX = 64;
     if (colvecs < 64) { TX = 1; while (TX < colvecs) TX *= 2; }
     const bool small = c.total / VEC < (int64_t)256 * 512;
+    int heavy = 0;
+    for (size_t n = 0; n < g.nodes.size(); n++) {
+        if (!live[n] || g.nodes[n].kind != NodeKind::Apply) continue;
+        switch (g.nodes[n].op) {
+        case EWF_EXP: case EWF_LOG: case EWF_LOG1P: case EWF_TANH: case EWF_SIGMOID: case EWF_EXPM1: heavy += 1; break;
+        case EWF_POW: case EWF_DIV: heavy += 2; break;
+        default: break;
+        }
+    }
+    // bytes that one element of the sweep moves, and the bytes of partial results of one column
+    std::vector<int> swept;
+    {
+        std::vector<int> tg;
+        for (int k : ew_out_ops) tg.push_back(g.outputs[c.ops[k].index].value);
+        for (int n : level) tg.push_back(g.nodes[n].args[0]);
+        swept = inputs_of(needed(tg));
+        swept.insert(swept.end(), ew_out_ops.begin(), ew_out_ops.end());
+    }
+    int64_t per_element = 0;
+    for (int k : swept) if (c.ops[k].stride[dR] != 0) per_element += isz(c.ops[k].storage);
+    per_element = std::max<int64_t>(per_element, 1);
+    // Rows per tile at which its partial results stay a thirty-second of what it moves: 128 bytes of
+    // every column for a plain sum, 8 rows for the LSTM cell's backward pass (16 streams, four sums).
+    const int64_t min_tile_rows = ceil_div((int64_t)32 * (int64_t)acc_bytes(level), per_element);
     // A small problem is bound by launches, not bandwidth: when one workgroup can take whole
-    // columns (a single reduced dimension of modest extent) the column strips are narrowed until
-    // there are enough workgroups, each folds its columns completely and writes the results
-    // itself -- one launch, no workspace.
+    // columns (a single reduced dimension, at most 192 KiB a workgroup, which a compute unit moves
+    // in about the time a second launch costs) the column strips are narrowed until there are
+    // enough workgroups, each folds its columns completely and writes the results itself -- one
+    // launch, no workspace.
     int nreduced = 0;
     for (int d = 0; d < R; d++) nreduced += c.reduced[d];
-    const bool whole_columns = small && nreduced == 1 && c.extent[dR] <= 1024 && e.opts.tile_elems <= 0;
-    if (whole_columns) {
+    bool whole_columns = false;
+    bool chained = false;                              // an accumulator that is a chain of dependent operations per element
+    for (int n : level) chained = chained || g.nodes[n].op == kRSumSqCentred || g.nodes[n].op == kRSumExpShifted;
+    // (less where the arithmetic of a column, on one compute unit, takes longer than its bytes: the
+    // LSTM cell's backward pass, hidden size 528, batch 208: one launch 9.5 us, two 8.3 us; batch 115
+    // 6.1 us against 8.2 us)
+    const int64_t whole_bytes = (chained ? 32 : heavy >= 4 ? 96 : 192) * 1024;
+    if (nreduced == 1 && e.opts.tile_elems <= 0) {
         int64_t other = 1;
         for (int d = 0; d < R - 1; d++) if (d != dR) other *= c.extent[d];
-        const int min_tx = std::max(1, 16 / VEC);
-        while (TX > min_tx && ceil_div(c.extent[in_d], (int64_t)TX * VEC) * other < 64) TX /= 2;
+        // (strips of at least 64 bytes of a row when the columns are long: float16 [3360, 192] summed
+        // over axis 0 in strips of 16 columns 7.1 us, two launches 5.6 us)
+        int narrowest = 4;
+        for (int k : swept) if (c.ops[k].stride[in_d] != 0) narrowest = std::min(narrowest, isz(c.ops[k].storage));
+        const int min_tx = small && c.extent[dR] <= 1024 ? std::max(1, 16 / VEC) : std::max(1, 64 / (VEC * narrowest));
+        int tx = TX;
+        while (tx > min_tx && (ceil_div(c.extent[in_d], (int64_t)tx * VEC) * other < 64 || c.extent[dR] * tx * VEC * per_element > whole_bytes)) tx /= 2;
+        whole_columns = c.extent[dR] * std::min<int64_t>(c.extent[in_d], (int64_t)tx * VEC) * per_element <= whole_bytes &&
+                        (small || c.total * per_element <= (int64_t)24 << 20);
+        if (whole_columns) TX = tx;
     }
     // Few columns and few rows: the lanes that neither would use take neighbouring indices of
     // the innermost other kept dimension (dK), TZ of them per workgroup, each with its own
@@ -79,18 +118,16 @@ ewf_status Gen::gen_col()
             TZ = block / (TX * TY);
         }
     }
-    const int64_t TK = std::min<int64_t>(c.extent[in_d], (int64_t)TX * VEC);   // columns per tile
+    // A workgroup that takes whole columns grows until a thread has one row of them: its
+    // trips are a chain of memory latencies.
+    if (whole_columns && TZ == 1 && e.opts.block_threads <= 0) {
+        while (block < (heavy >= 4 ? 512 : 1024) && c.extent[dR] > (int64_t)(block / TX) &&
+               (int64_t)(2 * block / 64 - 1) * TX * VEC * (int64_t)acc_bytes(level) <= 32 * 1024) block *= 2;
+        TY = block / TX;
+        p.block = block;
+    }
     // rows in flight per thread: four for streaming expressions, fewer when the expression is
     // heavy in transcendental operations (registers) or the problem is small (spread it out)
-    int heavy = 0;
-    for (size_t n = 0; n < g.nodes.size(); n++) {
-        if (!live[n] || g.nodes[n].kind != NodeKind::Apply) continue;
-        switch (g.nodes[n].op) {
-        case EWF_EXP: case EWF_LOG: case EWF_LOG1P: case EWF_TANH: case EWF_SIGMOID: case EWF_EXPM1: heavy += 1; break;
-        case EWF_POW: case EWF_DIV: heavy += 2; break;
-        default: break;
-        }
-    }
     int U = e.opts.unroll > 0 ? e.opts.unroll : small ? 1 : heavy >= 4 ? 2 : 4;
     // (with element-wise outputs, 16 elements per thread and trip: bias + ReLU + column sums on
     // float16 [401408, 256] took 91 us with two rows of eight in flight, 119 us with four)
@@ -118,6 +155,18 @@ ewf_status Gen::gen_col()
             U = rpt;
         }
     }
+    if (whole_columns && TZ == 1 && e.opts.unroll <= 0)
+        U = (int)std::max<int64_t>(1, std::min<int64_t>(ew_out_ops.empty() ? (VEC >= 4 ? 4 : 8) : heavy >= 4 ? 2 : std::max(1, 16 / VEC), ceil_div(c.extent[dR], TY)));
+    // A kernel with element-wise outputs that would leave compute units without work takes
+    // narrower strips (256 bytes of a float32 row at least): more workgroups for the same number of
+    // partial results.
+    if (!whole_columns && TZ == 1 && !ew_out_ops.empty() && e.opts.tile_elems <= 0 && e.opts.unroll <= 0) {
+        int64_t other = 1;
+        for (int d = 0; d < R - 1; d++) if (d != dR) other *= c.extent[d];
+        auto tiles = [&](int tx) { return other * ceil_div(c.extent[in_d], (int64_t)tx * VEC) * ceil_div(c.extent[dR], std::max<int64_t>((int64_t)(block / tx) * U, std::min<int64_t>(min_tile_rows, 32))); };
+        while (TX > 16 && tiles(TX) < (int64_t)2 * device_cu_count()) { TX /= 2; TY = block / TX; }
+    }
+    const int64_t TK = std::min<int64_t>(c.extent[in_d], (int64_t)TX * VEC);   // columns per tile
     int64_t T[kMaxDims];
     for (int d = 0; d < kMaxDims; d++) T[d] = 1;
     T[in_d] = TK;
@@ -135,10 +184,16 @@ ewf_status Gen::gen_col()
         const int64_t want = (int64_t)(ew_out_ops.empty() ? 5 : 48) * device_cu_count();
         const int64_t trip = (int64_t)TY * U;
         // (at least 128 bytes of every column per tile, or the partial results, one 4-byte value
-        // per column and tile, become a noticeable part of the traffic)
+        // per column and tile, become a noticeable part of the traffic -- unless that leaves
+        // compute units without work)
         int in_sz = 4;
         for (const Operand &op : c.ops) if (!op.is_output && op.stride[in_d] != 0) in_sz = std::min(in_sz, isz(op.storage));
-        const int64_t min_rows = std::max<int64_t>(trip, 128 / in_sz);
+        int64_t min_rows = std::max<int64_t>(trip, 128 / in_sz);
+        // (the LSTM cell's backward pass: [912, 1008] in 116 tiles 20.3 us, in 384 16.5 us; [1504, 560] in
+        // 141 19.7, in 384 15.7 us; [2736, 400] in 172 21.7, in 342 22.4 us)
+        const int64_t cus = device_cu_count(), fill = cus * 3 / 2;
+        if (other * ceil_div(c.extent[dR], min_rows) < cus * 5 / 8 && !ew_out_ops.empty())
+            min_rows = std::max({trip, std::min<int64_t>(min_tile_rows, min_rows), std::min(min_rows, c.extent[dR] * other / fill)});
         int64_t slices = std::max<int64_t>(1, std::min(ceil_div(want, other), ceil_div(c.extent[dR], min_rows)));
         if (whole_columns || TZ > 1) slices = 1;
         int64_t tr = ceil_div(c.extent[dR], slices);

@@ -1,0 +1,47 @@
+"""GPU parity of column kernels at the edges of their splits: whole columns in one workgroup of 256 to
+1024 threads, the first sizes that take partial results instead, narrow strips, and odd widths."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_ops_and_layouts import G, run_spec  # noqa: F401  (G is the fixture)
+from workloads import GraphSpec, configs as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,hidden", [(17, 33), (65, 130), (115, 464), (129, 512), (157, 537), (300, 208), (700, 350), (912, 1008), (2100, 36)])
+def test_lstm_backward_over_the_batch(batch, hidden, oracle, G):
+    w = wl.c2_lstm_cell_backward(batch=batch, hidden=hidden)
+    print(f"[case] lstm backward {batch} x {hidden}", flush=True)
+    expr, got = G.h.run_gpu(w)
+    assert expr.info()["kernel_class"] == "col", expr.info()
+    want = dict(zip(w.out_names, oracle.evaluate(w.oracle_spec or w.spec, wl.host_inputs(w), w.scalars, nthreads=8)))
+    for name, g, (rtol, atol) in zip(w.out_names, got, w.tol):
+        # A bias gradient sums `batch` gate gradients of either sign: a tree of at most 12 levels over
+        # chains of a few terms rounds by less than 24 * 2^-24 = 1.5e-6 of the sum of their
+        # magnitudes, plus what the terms themselves carry (the element-wise bar, 2e-6 of each); what
+        # they cancel to does not enter.
+        scale = np.abs(want[name.replace("dbias", "dz")].astype(np.float64)).sum(0, keepdims=True) if name.startswith("dbias") else None
+        G.h.compare(name, g, want[name], rtol, atol, scale=scale)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape,axes", [((60, 10000), (0,)), ((1000, 2000), (0,)), ((3000, 16), (0,)), ((3001, 17), (0,)), ((12289, 4), (0,)),
+                                        ((40, 1000, 64), (1,)), ((7, 513, 96), (1,)), ((257, 63), (0,))])
+def test_sums_and_extremes_down_columns(shape, axes, storage, oracle, G):
+    dt = np.float16 if storage == "f16" else np.float32
+    rng = np.random.default_rng(shape[0] + len(shape))
+    x = (rng.standard_normal(shape) * 2).astype(dt)
+    x.reshape(-1)[x.size // 3] = np.nan
+    s = GraphSpec(len(shape))
+    v = s.input(storage, (False,) * len(shape))
+    s.output(s.reduce("sum", s.apply("abs", v), axes), "f32")
+    s.output(s.reduce("max", v, axes), "f32")
+    s.output(s.reduce("argmax", v, axes), "i32")
+    print(f"[case] columns {storage} {shape} {axes}", flush=True)
+    expr, got = run_spec(G, s, [x])
+    assert expr.info()["kernel_class"] == "col", expr.info()
+    want = oracle.evaluate(s, [x], nthreads=4)
+    G.h.compare("sum", got[0], want[0], *G.h.REDUCTION)          # terms of one sign
+    np.testing.assert_array_equal(got[1], want[1])
+    np.testing.assert_array_equal(got[2], want[2])
