@@ -145,6 +145,21 @@ ewf_status generate(const Exec &e, Plan &p)
             }
         }
     }
+    // Several rows per wavefront: wide vectors at any alignment where the strict ones are single
+    // float32 elements, or float16 on rows of at least 512 bytes (softmax over float32 rows of 143 33.5 ->
+    // 28.0 us, 67 17.1 -> 14.5 us; float16 rows of 1001 56.9 -> 50.2 us; layer normalisation of float16 rows of
+    // 2324 42.0 -> 36.4 us, 1025 34.3 -> 28.0 us; the backward pass of bias + ReLU + channel sums on planes of
+    // 7 x 7 45.8 -> 38.5 us).  Short float16 rows (139 columns 7.8 against 8.6 us) and pairs of float32 (130
+    // columns 16.2 against 16.8 us) are faster as they are.
+    const bool lane_loose = narrowest == 4 ? c.vec == 1 : c.extent[c.rank - 1] * narrowest >= 512;
+    if (p.kclass == KernelClass::Lane && c.vec_loose > c.vec && lane_loose && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
+        // (the plan keeps reporting the width that the layout's alignment allows)
+        p.loose_vec = true;
+        Gen wide(e, p);
+        wide.VEC = c.vec_loose;
+        if (wide.gen_lane() == EWF_OK) return EWF_OK;
+        p.loose_vec = false;
+    }
     Gen gen(e, p);
     switch (p.kclass) {
     case KernelClass::Tile: return gen.gen_tile(false);

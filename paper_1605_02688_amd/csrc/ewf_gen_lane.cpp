@@ -23,12 +23,15 @@ ewf_status Gen::gen_lane()
     if (block % 64 || block > 1024) return fail("block_threads must be a multiple of 64, at most 1024");
     p.block = block;
     const int nin = g.ninputs;
-    if (cols % VEC) return fail("row length is not a multiple of the vector width");
+    // (vectors that assume element alignment only, the row's last one cut: see Plan::loose_vec)
+    const bool loose = p.loose_vec;
+    const bool ragged = loose && cols % VEC != 0;
+    if (cols % VEC && !loose) return fail("row length is not a multiple of the vector width");
     // lanes per row, vectors per lane
     int min_isz = 4;
     for (const Operand &op : c.ops) if (op.stride[in_d] != 0) min_isz = std::min(min_isz, isz(op.storage));
     int L = 1;
-    const int64_t nvec = cols / VEC;
+    const int64_t nvec = ceil_div(cols, VEC);
     if (cols * min_isz > 32) while (L < 64 && L < nvec) L *= 2;
     // more vectors than lanes (narrow vectors: an odd row length, or rows that are not aligned):
     // the lane count that leaves the fewest lane slots idle, with at most 16 vectors per lane
@@ -47,6 +50,26 @@ ewf_status Gen::gen_lane()
             if (best_waste < 0 || waste < best_waste) { best_waste = waste; L = l; }
         }
     }
+    // Wide vectors that leave many of those lanes idle (34 vectors of a row on 64 lanes): fewer lanes
+    // with several vectors each, at a small price per halving.  Float32 rows that are written back
+    // keep their lanes, whose stores are then whole lines.  (Sums over rows of 144 float32, 142 MB,
+    // 36.3 -> 24.6 us, 288 float16 37.7 -> 24.8 us; softmax over 272 float16 16.3 -> 13.0 us, 80 float16 21.1
+    // -> 17.3 us; but 200 float32 18.7 -> 25.1 us, 80 float32 24.6 -> 29.8 us.)
+    bool writes_rows = false;
+    for (const OutputDecl &od : g.outputs) writes_rows = writes_rows || (g.nodes[od.value].bcast & red.axes) != red.axes;
+    if (nvec <= 64 && VEC * min_isz >= 16 && L >= 8 && (!writes_rows || min_isz == 2)) {
+        int vec_regs = 0;
+        for (int k = 0; k < nin; k++)
+            if (c.ops[k].stride[in_d] != 0 && live[g.input_node[k]]) vec_regs += (VEC * isz(c.ops[k].storage) + 3) / 4;
+        double best = (double)L;
+        const int top = L;
+        for (int l = top / 2; l >= 4; l /= 2) {
+            const int64_t nv = ceil_div(nvec, (int64_t)l);
+            if (nv * vec_regs > 48) break;
+            const double cost = (double)(nv * l) * (l == 4 ? 1.2 : l == 8 ? 1.1 : 1.05);
+            if (cost < best) { best = cost; L = l; }
+        }
+    }
     // ... but at least 16 bytes of the row per lane: where the row length or the alignment allows
     // only narrow accesses, a lane with a single one in flight leaves the memory system idle
     // (rows of 49 float32, one element per lane: 2.9 TB/s)
@@ -56,7 +79,9 @@ ewf_status Gen::gen_lane()
     if (L == 2 && VEC * min_isz < 16 && cols / VEC <= 32) L = 1;
     const int64_t NV = ceil_div(cols, (int64_t)L * VEC);
     const bool ragged_cols = NV * L * VEC != cols;
-
+    const int64_t NFULL = cols / ((int64_t)L * VEC);        // steps whose vectors all lie inside the row, in every lane
+    const std::string cut_len = std::to_string(cols % VEC);
+    const std::string skip_outside = ragged ? "                if (j >= " + std::to_string(NFULL) + " && col + e_ >= " + std::to_string(cols) + ") continue;\n" : "";
     // ---- roles of the outputs
     std::vector<int> full_out_ops, group_out_ops, final_out_ops;
     for (size_t k = nin; k < c.ops.size(); k++) {
@@ -139,14 +164,29 @@ ewf_status Gen::gen_lane()
         o << "        #pragma unroll\n        for (int j = 0; j < " << NV << "; ++j) {\n";
         o << "            const int col = (j * " << L << " + lr) * EWF_VEC;\n";
         if (ragged_cols) o << "            if (col >= " << cols << ") continue;\n";
-        if (op.access == Access::Vector)
+        if (op.access == Access::Vector && loose) {
+            // (the row's last vector is read as its last VEC elements and moved into place below,
+            // behind all the loads)
+            o << "            x_" << nm << "[j] = ewf_ld_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + "
+              << (ragged ? "(j >= " + std::to_string(NFULL) + " && col > " + std::to_string(cols - VEC) + " ? " + std::to_string(cols - VEC) + " : col)" : std::string("col")) << ");\n";
+        }
+        else if (op.access == Access::Vector)
             // (ordinary loads even for operands touched once: with one thread per row the vectors of
             // a row are separate instructions that share cache lines -- rows of 8 floats 26.3 us with
             // non-temporal loads, 22.5 us without; 32 columns 50.7 against 45.3 us)
             o << "            x_" << nm << "[j] = ewf_ld<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col);\n";
         else
             o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) x_" << nm << "[j].e[e_] = q_" << nm
-              << "[(idx_t)(col + e_) * p.st_" << nm << "[" << in_d << "]];\n";
+              << "[(idx_t)" << (ragged ? "(col + e_ < " + std::to_string(cols) + " ? col + e_ : " + std::to_string(cols - 1) + ")" : std::string("(col + e_)"))
+              << " * p.st_" << nm << "[" << in_d << "]];\n";
+        o << "        }\n";
+    }
+    if (ragged && NFULL < NV) {
+        o << "        #pragma unroll\n        for (int j = " << NFULL << "; j < " << NV << "; ++j) {\n";
+        o << "            const bool cut_ = (j * " << L << " + lr) * EWF_VEC > " << cols - VEC << ";\n";
+        for (int k : row_ops)
+            if (c.ops[k].access == Access::Vector)
+                o << "            x_" << opname(k) << "[j] = ewf_move_cut<" << ctype(c.ops[k].storage) << ", EWF_VEC, " << cut_len << ">(x_" << opname(k) << "[j], cut_);\n";
         o << "        }\n";
     }
 
@@ -187,6 +227,7 @@ ewf_status Gen::gen_lane()
         o << "            const int col = (j * " << L << " + lr) * EWF_VEC;\n";
         if (ragged_cols) o << "            if (col >= " << cols << ") continue;\n";
         o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
+        o << skip_outside;
         emit_values(need, cx, "                ");
         // a lane walks its columns in increasing order
         emit_accumulate(av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
@@ -217,10 +258,19 @@ ewf_status Gen::gen_lane()
         for (int k : full_out_ops) {
             const Operand &op = c.ops[k];
             std::string nm = opname(k);
-            if (op.access == Access::Vector)
+            if (op.access == Access::Vector && loose) {
+                // (ordinary stores: rows at any alignment share lines, and non-temporal stores of
+                // parts of a line cost more -- softmax over float16 rows of 1292 58.1 against 49.6 us)
+                if (ragged) {
+                    o << "            if (j < " << NFULL << " || col <= " << cols - VEC << ") ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << ");\n";
+                    o << "            else ewf_st_cut<" << ctype(op.storage) << ", EWF_VEC, " << cut_len << ">(q_" << nm << " + col, y_" << nm << ");\n";
+                }
+                else o << "            ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << ");\n";
+            }
+            else if (op.access == Access::Vector)
                 o << "            " << (op.stream ? "ewf_st_nt<" : "ewf_st<") << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << ");\n";
             else
-                o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) q_" << nm << "[(idx_t)(col + e_) * p.st_" << nm
+                o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) " << (ragged ? "if (col + e_ < " + std::to_string(cols) + ") " : std::string("")) << "q_" << nm << "[(idx_t)(col + e_) * p.st_" << nm
                   << "[" << in_d << "]] = y_" << nm << ".e[e_];\n";
         }
         o << "        }\n";

@@ -1,0 +1,43 @@
+"""GPU parity of short rows held by a few lanes of a wavefront: rows that end inside a vector, every
+remainder, and the lane counts that wide vectors are spread over."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_ops_and_layouts import G, run_spec  # noqa: F401  (G is the fixture)
+from workloads import GraphSpec
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("storage,cols", [("f32", c) for c in (17, 18, 49, 67, 143, 144, 179, 321, 999, 1001, 1023)] +
+                         [("f16", c) for c in (80, 139, 257, 258, 259, 260, 261, 262, 263, 272, 288, 400, 1001, 1292, 2044)])
+def test_softmax_sum_and_argmax_of_short_rows(storage, cols, oracle, G):
+    dt = np.float16 if storage == "f16" else np.float32
+    rng = np.random.default_rng(cols)
+    rows = 4097
+    x = (rng.standard_normal((rows, cols)) * 2).astype(dt)
+    x[5] = np.nan                                               # never read into a neighbouring row's result
+    x[7, cols - 1] = 30.0                                       # the maximum in the last element
+    s = GraphSpec(2)
+    xi = s.input(storage, (False, False))
+    m = s.reduce("max", xi, (1,), keep=True)
+    e = s.apply("exp", s.sub(xi, m))
+    s.output(s.div(e, s.reduce("sum", e, (1,), keep=True)), storage)
+    s.output(s.reduce("argmax", xi, (1,)), "i32")
+    print(f"[case] softmax {storage} {rows} x {cols}", flush=True)
+    expr, got = run_spec(G, s, [x])
+    assert expr.info()["kernel_class"] == "lane", expr.info()
+    want = oracle.evaluate(s, [x], nthreads=8)
+    bar = G.h.HALF if storage == "f16" else G.h.REDUCTION
+    G.h.compare("p", got[0], want[0], *bar)
+    G.h.compare("argmax", got[1], want[1], 0, 0)
+    assert got[1][7] == cols - 1
+    s = GraphSpec(2)
+    xi = s.input(storage, (False, False))
+    s.output(s.reduce("sum", s.apply("abs", xi), (1,)), "f32")
+    s.output(s.reduce("min", xi, (1,)), "f32")
+    x[5] = 1.0
+    expr, got = run_spec(G, s, [x])
+    want = oracle.evaluate(s, [x], nthreads=8)
+    G.h.compare("sum", got[0], want[0], *G.h.REDUCTION)          # terms of one sign
+    G.h.compare("min", got[1], want[1], 0, 0)
