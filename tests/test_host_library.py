@@ -848,3 +848,19 @@ def test_an_empty_plan_checks_the_pointers_it_fills_on_every_call():
     with pytest.raises(ewf.EwfError) as err:
         e.run(ins, [ref(0, (5,))])
     assert err.value.status == ewf.EINVAL
+
+
+def test_packed_launch_arguments_equal_the_marshalled_ones():
+    """The launch path's argument records against those of the planning calls: ranks 0 to 8, views,
+    empty lists, extents given as other whole numbers."""
+    import ctypes
+    tensors = [ref(BASE, (3, 5), (1, 3)), ref(BASE + 64, ()), ref(BASE + 128, (2,) * 8), ref(BASE + 256, (7, 1, 0)),
+               ewf.TensorRef(BASE + 512, (np.int64(4), 2.0), (np.int64(2), 1.0))]
+    for group in (tensors, tensors[1:2], tensors[::-1], []):
+        want, _k = ewf._marshal(group)
+        first, _keep = ewf._pack(group)
+        got = ctypes.cast(first, ctypes.POINTER(ewf.ewf_tensor))
+        for k, t in enumerate(group):
+            rank = len(t.shape)
+            assert got[k].ptr == want[k].ptr and bool(got[k].shape) and bool(got[k].strides)
+            assert got[k].shape[:rank] == want[k].shape[:rank] and got[k].strides[:rank] == want[k].strides[:rank]
