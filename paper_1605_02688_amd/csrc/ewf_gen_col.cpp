@@ -376,8 +376,19 @@ ewf_status Gen::gen_col()
             o << in2 << "if (tid >= 64 && (tid & 63) < EWF_TX) { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) sm_col[(((tid >> 6) - 1) * EWF_TX + tx) * EWF_VEC + e_] = acc[e_]; }\n";
             o << in2 << "__syncthreads();\n";
             o << in2 << "if (tid < EWF_TX) {\n";
-            o << in2 << "    for (int w_ = 0; w_ < EWF_NWAVES - 1; ++w_)\n";
-            o << in2 << "        _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], sm_col[(w_ * EWF_TX + tx) * EWF_VEC + e_]);\n";
+            if (NW <= 4) {
+                o << in2 << "    for (int w_ = 0; w_ < EWF_NWAVES - 1; ++w_)\n";
+                o << in2 << "        _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], sm_col[(w_ * EWF_TX + tx) * EWF_VEC + e_]);\n";
+            } else {
+                // (many wavefronts meet in a tree: a chain of fifteen sums would round more often
+                // than the longer trips of a small workgroup did)
+                o << in2 << "    _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
+                o << in2 << "        Acc w_[EWF_NWAVES];\n" << in2 << "        w_[0] = acc[e_];\n";
+                o << in2 << "        _Pragma(\"unroll\") for (int i_ = 1; i_ < EWF_NWAVES; ++i_) w_[i_] = sm_col[((i_ - 1) * EWF_TX + tx) * EWF_VEC + e_];\n";
+                o << in2 << "        _Pragma(\"unroll\") for (int s_ = 1; s_ < EWF_NWAVES; s_ *= 2)\n";
+                o << in2 << "            _Pragma(\"unroll\") for (int i_ = 0; i_ + s_ < EWF_NWAVES; i_ += 2 * s_) w_[i_] = Acc_combine()(w_[i_], w_[i_ + s_]);\n";
+                o << in2 << "        acc[e_] = w_[0];\n" << in2 << "    }\n";
+            }
             o << in2 << "}\n";
         }
         o << in2 << "if (" << (TZ > 1 ? "ty == 0" : "tid < EWF_TX") << " && " << okname << ") {\n";
@@ -485,8 +496,15 @@ ewf_status Gen::gen_col()
     o << "\nextern \"C\" __global__ void __launch_bounds__(256) ewf_finish(const Params p)\n{\n";
     o << "    const Acc *const partials = (const Acc *)p.ws_partials;\n";
     o << "    for (idx_t group = blockIdx.x * 256 + threadIdx.x; group < p.nrows; group += gridDim.x * 256) {\n";
-    o << "        Acc tot = partials[group];\n";
-    o << "        _Pragma(\"unroll 8\") for (idx_t s_ = 1; s_ < p.nslots; ++s_) tot = Acc_combine()(tot, partials[(size_t)s_ * (size_t)p.nrows + (size_t)group]);\n";
+    // (four chains, met at the end: a quarter of the roundings and of the dependent operations of one)
+    o << "        Acc a_[4];\n";
+    o << "        _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) a_[i_] = Acc_identity();\n";
+    o << "        idx_t s_ = 0;\n";
+    o << "        _Pragma(\"unroll 2\") for (; s_ + 4 <= p.nslots; s_ += 4) {\n";
+    o << "            _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) a_[i_] = Acc_combine()(a_[i_], partials[(size_t)(s_ + i_) * (size_t)p.nrows + (size_t)group]);\n";
+    o << "        }\n";
+    o << "        for (; s_ < p.nslots; ++s_) a_[0] = Acc_combine()(a_[0], partials[(size_t)s_ * (size_t)p.nrows + (size_t)group]);\n";
+    o << "        const Acc tot = Acc_combine()(Acc_combine()(a_[0], a_[1]), Acc_combine()(a_[2], a_[3]));\n";
     o << "        idx_t g_ = group;\n";
     for (int d = R - 1; d >= 0; d--) {
         if (c.reduced[d]) { o << "        const idx_t o" << d << " = 0;\n"; continue; }

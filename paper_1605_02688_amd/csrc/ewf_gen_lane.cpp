@@ -57,6 +57,7 @@ ewf_status Gen::gen_lane()
     // -> 17.3 us; but 200 float32 18.7 -> 25.1 us, 80 float32 24.6 -> 29.8 us.)
     bool writes_rows = false;
     for (const OutputDecl &od : g.outputs) writes_rows = writes_rows || (g.nodes[od.value].bcast & red.axes) != red.axes;
+    const int all_lanes = L;
     if (nvec <= 64 && VEC * min_isz >= 16 && L >= 8 && (!writes_rows || min_isz == 2)) {
         int vec_regs = 0;
         for (int k = 0; k < nin; k++)
@@ -70,6 +71,7 @@ ewf_status Gen::gen_lane()
             if (cost < best) { best = cost; L = l; }
         }
     }
+    const bool took_over = L < all_lanes;              // a lane holds the vectors of several
     // ... but at least 16 bytes of the row per lane: where the row length or the alignment allows
     // only narrow accesses, a lane with a single one in flight leaves the memory system idle
     // (rows of 49 float32, one element per lane: 2.9 TB/s)
@@ -223,15 +225,25 @@ ewf_status Gen::gen_lane()
         for (int n : lvl[l]) tg.push_back(g.nodes[n].args[0]);
         std::vector<char> need = needed(tg);
         o << "        " << an << " " << av << " = " << an << "_identity();\n";
+        // Where a lane took over the vectors of others, a vector's terms are added to each other first
+        // and the vectors to four chains: no more roundings on a path than the lanes it replaces had
+        // (sums over rows of 144 float32: relative error 6.6e-8 in one chain of 36, 4.8e-8 before).
+        bool chains = took_over && NV >= 3;
+        for (int n : lvl[l]) chains = chains && g.nodes[n].op == EWF_RSUM;
+        if (chains) o << "        " << an << " sub" << l << "_[4];\n        _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) sub" << l << "_[i_] = " << an << "_identity();\n";
         o << "        #pragma unroll\n        for (int j = 0; j < " << NV << "; ++j) {\n";
         o << "            const int col = (j * " << L << " + lr) * EWF_VEC;\n";
         if (ragged_cols) o << "            if (col >= " << cols << ") continue;\n";
+        if (chains) o << "            " << an << " part_ = " << an << "_identity();\n";
         o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
         o << skip_outside;
         emit_values(need, cx, "                ");
         // a lane walks its columns in increasing order
-        emit_accumulate(av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
-        o << "            }\n        }\n";
+        emit_accumulate(chains ? std::string("part_") : av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
+        o << "            }\n";
+        if (chains) o << "            sub" << l << "_[j & 3] = " << an << "_combine()(sub" << l << "_[j & 3], part_);\n";
+        o << "        }\n";
+        if (chains) o << "        " << av << " = " << an << "_combine()(" << an << "_combine()(sub" << l << "_[0], sub" << l << "_[1]), " << an << "_combine()(sub" << l << "_[2], sub" << l << "_[3]));\n";
         emit_first_index(av, lvl[l], "lr * EWF_VEC < " + std::to_string(cols), "lr * EWF_VEC", "        ");
         // the lanes of a row fold with a fixed butterfly; afterwards each holds the row's result
         for (int m = 1; m < L; m *= 2)

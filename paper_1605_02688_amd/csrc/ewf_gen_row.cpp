@@ -386,11 +386,19 @@ ewf_status Gen::gen_row()
         o << "        " << an << " " << av << " = " << an << "_identity();\n";
         open_pass();
         stream_loads(need);
+        // Sums over many vectors per thread: a vector's terms are added to each other first, so that the
+        // chain of roundings is as long as the thread has vectors, not elements (thirteen against
+        // fifty-two for the gradient of softmax cross-entropy on rows of 50257, whose sums would
+        // otherwise round more often than those of rows split over workgroups).
+        bool by_vector = resident && regs > 48;
+        for (int n : lvl[l]) by_vector = by_vector && g.nodes[n].op == EWF_RSUM;
+        if (by_vector) o << "            " << an << " part_ = " << an << "_identity();\n";
         o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
         if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
         emit_values(need, cx, "                ");
-        emit_accumulate(av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
+        emit_accumulate(by_vector ? std::string("part_") : av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
         o << "            }\n";
+        if (by_vector) o << "            " << av << " = " << an << "_combine()(" << av << ", part_);\n";
         close_pass();
         // every thread walks its columns in increasing order, starting at tid * EWF_VEC
         emit_first_index(av, lvl[l], "(idx_t)tid * EWF_VEC < cols", "tid * EWF_VEC", "        ");

@@ -41,3 +41,25 @@ def test_softmax_sum_and_argmax_of_short_rows(storage, cols, oracle, G):
     want = oracle.evaluate(s, [x], nthreads=8)
     G.h.compare("sum", got[0], want[0], *G.h.REDUCTION)          # terms of one sign
     G.h.compare("min", got[1], want[1], 0, 0)
+
+
+@pytest.mark.parametrize("storage,cols", [("f16", 160), ("f16", 221), ("f16", 272), ("f16", 1025), ("f32", 144), ("f32", 179), ("f32", 749)])
+def test_layer_normalisation_of_short_rows(storage, cols, oracle, G):
+    # two levels of sums over the registers of a lane, operands that vary along the row only
+    dt = np.float16 if storage == "f16" else np.float32
+    rng = np.random.default_rng(cols)
+    x = (rng.standard_normal((4099, cols)) * 2).astype(dt)
+    gb = [rng.uniform(0.5, 1.5, (1, cols)).astype(dt), rng.uniform(-0.5, 0.5, (1, cols)).astype(dt)]
+    s = GraphSpec(2)
+    xi = s.input(storage, (False, False))
+    ga, be = s.input(storage, (True, False)), s.input(storage, (True, False))
+    cen = s.sub(xi, s.mul(s.reduce("sum", xi, (1,), keep=True), s.const(1.0 / cols)))
+    var = s.mul(s.reduce("sum", s.apply("sqr", cen), (1,), keep=True), s.const(1.0 / cols))
+    s.output(s.add(s.mul(s.mul(cen, s.apply("recip", s.apply("sqrt", s.add(var, s.const(1e-5))))), ga), be), storage)
+    print(f"[case] layer normalisation {storage} 4099 x {cols}", flush=True)
+    expr, got = run_spec(G, s, [x] + gb)
+    assert expr.info()["kernel_class"] == "lane", expr.info()
+    want = oracle.evaluate(s, [x] + gb, nthreads=8)
+    # the subtraction of the mean cancels: relative to |x| + |mean| over the deviation, here below 8
+    bar = G.h.HALF if storage == "f16" else G.h.REDUCTION
+    G.h.compare("normalised", got[0], want[0], bar[0], 8 * bar[1])
