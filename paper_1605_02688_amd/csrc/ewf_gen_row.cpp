@@ -207,7 +207,7 @@ ewf_status Gen::gen_row()
     };
     // Vectors that assume element alignment only (see Plan::loose_vec): a row may start at any
     // element, and when its length is no whole number of vectors the last one is cut (`ragged`)
-    // and handled element by element.  The steps below NFULL hold whole vectors for every thread,
+    // and moved into place (ewf_move_cut).  The steps below NFULL hold whole vectors for every thread,
     // which the unrolled code knows at compile time.
     const bool loose = p.loose_vec;
     const bool ragged = loose && cols % VEC != 0;

@@ -58,7 +58,7 @@ ewf_status Gen::gen_tile(bool with_reduce)
 
     // Vectors that assume element alignment only (see Plan::loose_vec): whole vectors of a row are
     // read and written wide wherever the row starts; a row that ends inside a vector has that
-    // last vector handled element by element (`ragged`).
+    // last vector cut (`ragged`).
     const bool loose = p.loose_vec;
     const bool ragged = loose && c.extent[R - 1] % VEC != 0;
     auto streamed = [&](const Operand &op) { return op.stream && VEC * isz(op.storage) % 16 == 0 ? ", ewf_streamed()" : ""; };

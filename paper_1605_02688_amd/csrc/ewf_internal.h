@@ -214,7 +214,7 @@ struct Plan {
     bool empty = false;                  // zero-size iteration space: nothing to traverse
     // The kernel was generated for canon.vec_loose: rows may start at any element and end inside
     // a vector.  Whole vectors are read and written with accesses that assume element alignment
-    // only, the last vector of a row element by element.
+    // only, the last vector of a row moved into place.
     bool loose_vec = false;
     int strict_vec = 0;                  // canon.vec as the canonicaliser set it (0: not recorded yet)
     struct Fill { int output; int rank; int elem_bytes; uint32_t bits; };
