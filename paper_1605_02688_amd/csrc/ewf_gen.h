@@ -381,12 +381,15 @@ struct Gen {
             case kRSumSqCentred:
                 // two groups of elements become one: the means meet at their weighted average and
                 // the distance between them adds to the squared deviations
+                // (a group without elements leaves the other as it is, to the bit: its mean of 0 is no
+                // mean, and the squared distance to it overflows for a mean above 1.8e19)
                 o << "        { const float n_ = x.n" << i << " + y.n" << i << ";\n"
                   << "          const float r_ = n_ > 0.0f ? 1.0f / n_ : 0.0f;\n"
                   << "          const float d_ = " << b << " - " << a << ";\n"
                   << "          r.n" << i << " = n_;\n"
-                  << "          r.a" << i << " = " << a << " + d_ * (y.n" << i << " * r_);\n"
-                  << "          r.b" << i << " = x.b" << i << " + y.b" << i << " + d_ * d_ * (x.n" << i << " * y.n" << i << " * r_); }\n";
+                  << "          const float w_ = x.n" << i << " * y.n" << i << " * r_;\n"
+                  << "          r.a" << i << " = x.n" << i << " > 0.0f ? " << a << " + d_ * (y.n" << i << " * r_) : " << b << ";\n"
+                  << "          r.b" << i << " = x.b" << i << " + y.b" << i << " + (w_ > 0.0f ? d_ * d_ * w_ : 0.0f); }\n";
                 break;
             case EWF_RARGMAX: {
                 std::string ia = "x.i" + std::to_string(i), ib = "y.i" + std::to_string(i);

@@ -3,7 +3,7 @@
 import numpy as np
 import pytest
 
-from tests.test_gpu_ops_and_layouts import G, run_spec  # noqa: F401  (G is the fixture)
+from tests.test_gpu_ops_and_layouts import G, _moments_spec, run_spec  # noqa: F401  (G is the fixture)
 from workloads import GraphSpec, configs as wl
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +45,18 @@ def test_sums_and_extremes_down_columns(shape, axes, storage, oracle, G):
     G.h.compare("sum", got[0], want[0], *G.h.REDUCTION)          # terms of one sign
     np.testing.assert_array_equal(got[1], want[1])
     np.testing.assert_array_equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("shape,axes", [((2048, 8192), (0,)), ((65536, 64), (0,)), ((200, 2000), (0,)), ((5, 4096), (0,)), ((33, 7, 640), (0,)), ((3, 300000), (1,))])
+def test_variance_about_a_huge_mean(shape, axes, G):
+    """A mean whose square overflows: folds that meet groups without elements (lanes without rows, chains
+    without partial results) must not form the distance to them."""
+    rng = np.random.default_rng(shape[0])
+    x = (1e20 + 3e16 * rng.standard_normal(shape)).astype(np.float32)
+    n = int(np.prod([shape[d] for d in axes]))
+    print(f"[case] moments {shape} over {axes} around 1e20", flush=True)
+    _expr, got = run_spec(G, _moments_spec(len(shape), axes, n, "f32", False), [x])
+    # Deviations are taken from a running mean, a float32 number near 1e20, and rounded with it: off
+    # by up to a few of its spacings (8.8e12), four against a deviation of 3e16 change a squared
+    # deviation by 2 * 4 * 8.8e12 / 3e16 = 2.3e-3 at worst.
+    G.h.compare("var", got[1], x.astype(np.float64).var(axes, keepdims=True).astype(np.float32), 2.5e-3, 0)
