@@ -730,6 +730,10 @@ struct Gen {
     }
 
     int auto_waves_per_simd = 0;              // register budget the generator itself asks for
+    // A staged tile whose copies did not fit the LDS is shaped again: with at most this many elements
+    // (0: the ordinary budget), in the end without staging.
+    int64_t stage_cap = 0;
+    bool lds_refused = false;
 
     std::string occupancy_attr() const
     {

@@ -148,10 +148,11 @@ ewf_status Gen::gen_tile(bool with_reduce)
     std::vector<int> staged;                           // operand numbers
     std::vector<int> sdims;                            // dims ordered by the staged operand's stride
     int VS = 1;
-    if (!with_reduce && !e.opts.no_lds_staging) {
+    if (!with_reduce && !e.opts.no_lds_staging && !lds_refused) {
         const int k = permuted_operand();
         if (k >= 0) staged.push_back(k);
     }
+    int64_t budget = 0;                                // elements of a staged tile
     int64_t ST[kMaxDims];                              // the part of the tile that is staged: without the tile's padding, pieces whole
     bool stage_loose = false;                          // pieces that assume element alignment only, the last of a run moved back to end with it
     if (!staged.empty()) {
@@ -175,9 +176,10 @@ ewf_status Gen::gen_tile(bool with_reduce)
         // better (x + y^T on float32 [64, 100000] in 392 tiles 16.3 us, in 1042 19.2 us; [8, 512, 512] in
         // 128 6.0, in 512 6.8 us; but [1024, 1024] in 64 5.3, in 512 4.1 us).
         const int64_t full_tile = 65536 / szS;
-        const int64_t budget = e.opts.tile_elems > 0 ? e.opts.tile_elems
-                               : heavy < 4 && c.total >= device_cu_count() / 2 * full_tile ? full_tile
-                               : std::min(full_tile, std::max<int64_t>(2048, c.total / ((int64_t)4 * device_cu_count())));
+        budget = e.opts.tile_elems > 0 ? e.opts.tile_elems
+                 : heavy < 4 && c.total >= device_cu_count() / 2 * full_tile ? full_tile
+                 : std::min(full_tile, std::max<int64_t>(2048, c.total / ((int64_t)4 * device_cu_count())));
+        if (stage_cap > 0) budget = std::min(budget, stage_cap);
         for (int d = 0; d < kMaxDims; d++) T[d] = 1;
         // Runs of at least 128 bytes along the staged operand's memory order; 64 where the tile's
         // runs along the output's order cannot be whole lines (see shares_lines): the dies then
@@ -209,7 +211,7 @@ ewf_status Gen::gen_tile(bool with_reduce)
             int64_t cap = std::max<int64_t>(1, budget / others);
             // (a row that is a little longer than a small tile's share is taken whole rather than
             // in two tiles, the second nearly empty)
-            if (d == R - 1 && e.opts.tile_elems <= 0 && c.extent[d] > cap && c.extent[d] * 2 <= cap * 3 && others * (c.extent[d] + VEC) * szS <= 65536) cap = c.extent[d] + VEC;
+            if (d == R - 1 && e.opts.tile_elems <= 0 && c.extent[d] > cap && c.extent[d] * 2 <= cap * 3 && others * (c.extent[d] + VEC) * szS <= (stage_cap > 0 ? stage_cap * szS : 65536)) cap = c.extent[d] + VEC;
             int64_t t = std::max<int64_t>(T[d], std::min<int64_t>(c.extent[d], cap));
             if (t < c.extent[d]) {
                 // prefer a split whose runs in the contiguous operands are whole 128-byte lines
@@ -366,6 +368,15 @@ ewf_status Gen::gen_tile(bool with_reduce)
         }
         for (int d = 0; d < R; d++) if (LS[d] >= LS[s0]) LSP[d] = LS[d] / LS[s0] * (LS[s0] + lds_pad);
         lds_elems = lds_elems / LS[s0] * (LS[s0] + lds_pad);
+        // Every staged operand has a copy of its own, padding included: where several share the
+        // tile (from three full ones on, or two whose short runs are padded by half) the tile is
+        // made smaller until all copies fit the 160 KiB that a workgroup can have.
+        const int64_t lds_limit = 160 * 1024, used = lds_elems * szS * (int64_t)staged.size();
+        if (used > lds_limit) {
+            stage_cap = std::min(budget * 3 / 4, (int64_t)((double)budget * (double)lds_limit / (double)used));
+            if (stage_cap < 512) lds_refused = true;       // (more operands than copies of the smallest tile fit)
+            return gen_tile(with_reduce);
+        }
     }
 
     int64_t TE = 1;

@@ -42,3 +42,24 @@ def test_sum_with_a_transposed_operand(shape, storage, oracle, G):
     want = oracle.evaluate(s, [a, b, r], nthreads=4)
     # one product and one sum of either sign: relative to the magnitudes of the two terms
     G.h.compare("sum", got[0], want[0], *G.h.ELEMENTWISE, scale=np.abs(a.astype(np.float64) * r) + np.abs(b.astype(np.float64)))
+
+
+@pytest.mark.parametrize("storage,shape,order,copies", [("f16", (1001, 1003), (1, 0), 3), ("f16", (1001, 1003), (1, 0), 4), ("f32", (640, 512), (1, 0), 3), ("f32", (300, 301), (1, 0), 7),
+                                                        ("f16", (25, 300, 16, 3), (1, 0, 3, 2), 2), ("f16", (51, 288, 7), (0, 2, 1), 4), ("f16", (4, 59, 82, 113), (0, 3, 1, 2), 5)])
+def test_several_permuted_operands_share_a_tile(storage, shape, order, copies, oracle, G):
+    dt = np.float16 if storage == "f16" else np.float32
+    rng = np.random.default_rng(copies)
+    back = [order.index(d) for d in range(len(shape))]
+    xs = [rng.standard_normal(shape).astype(dt)] + [rng.standard_normal([shape[d] for d in order]).astype(dt).transpose(back) for _ in range(copies)]
+    s = GraphSpec(len(shape))
+    v = s.input(storage, (False,) * len(shape))
+    for k in range(copies):
+        v = s.add(v, s.mul(s.input(storage, (False,) * len(shape)), s.const(0.5 ** k)))
+    s.output(v, "f32")
+    print(f"[case] {copies} permuted operands {storage} {shape}", flush=True)
+    expr, got = run_spec(G, s, xs)
+    assert expr.info()["staged_operands"] == copies and expr.info()["lds_bytes"] <= 160 * 1024, expr.info()
+    want = oracle.evaluate(s, xs, nthreads=4)
+    # sums of either sign: relative to the magnitudes of the terms
+    scale = np.abs(xs[0].astype(np.float64)) + sum(0.5 ** k * np.abs(x.astype(np.float64)) for k, x in enumerate(xs[1:]))
+    G.h.compare("sum", got[0], want[0], *G.h.ELEMENTWISE, scale=scale)

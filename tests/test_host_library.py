@@ -864,3 +864,27 @@ def test_packed_launch_arguments_equal_the_marshalled_ones():
             rank = len(t.shape)
             assert got[k].ptr == want[k].ptr and bool(got[k].shape) and bool(got[k].strides)
             assert got[k].shape[:rank] == want[k].shape[:rank] and got[k].strides[:rank] == want[k].strides[:rank]
+
+
+@pytest.mark.parametrize("storage", ["f16", "f32"])
+@pytest.mark.parametrize("shape,order,copies", [((4001, 4003), (1, 0), 3), ((4001, 4003), (1, 0), 4), ((2048, 2048), (1, 0), 3), ((2048, 2048), (1, 0), 9),
+                                                ((64, 100003), (1, 0), 5), ((250, 3000, 16, 3), (1, 0, 3, 2), 2), ((51, 288, 7), (0, 2, 1), 4),
+                                                ((24, 109, 82, 113), (0, 3, 1, 2), 5), ((300, 301), (1, 0), 40)])
+def test_copies_of_several_permuted_operands_share_the_lds(shape, order, copies, storage):
+    """Every operand staged for a tile takes a copy of it, padding included; together they stay
+    within what a workgroup can have, also where a caller asks for large tiles."""
+    nd = len(shape)
+    strides, acc = [0] * nd, 1
+    for d in reversed(order):                                   # `order`: the operands' dimensions, slowest in memory first
+        strides[d], acc = acc, acc * shape[d]
+    s = GraphSpec(nd)
+    v = s.input(storage, (False,) * nd)
+    for _ in range(copies):
+        v = s.add(v, s.input(storage, (False,) * nd))
+    s.output(v, storage)
+    ins = [ref(BASE, shape)] + [ref(BASE + ((k + 1) << 32), shape, strides) for k in range(copies)]
+    for opts in ({}, {"tile_elems": 40000}):
+        e = ewf.Expression(s, **opts)
+        e.plan(ins, [ref(BASE + (100 << 32), shape)])
+        info = e.info()
+        assert info["kernel_class"] == "tile" and info["staged_operands"] == copies and info["lds_bytes"] <= 160 * 1024, info
