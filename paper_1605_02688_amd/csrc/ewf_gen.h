@@ -491,6 +491,82 @@ struct Gen {
         }
     }
 
+    // Slots whose result is rounded at every step, in whatever order the elements meet: one flag
+    // per position of `nodes` for float32 sums and products, and with `chained` for the single-pass
+    // accumulators.  Extremes are exact and are never flagged.
+    std::vector<char> rounded_slots(const std::vector<int> &nodes, bool chained) const
+    {
+        std::vector<char> f(nodes.size(), 0);
+        for (size_t i = 0; i < nodes.size(); i++) {
+            const Node &nd = g.nodes[nodes[i]];
+            if (g.nodes[nd.args[0]].vtype != EWF_F32) continue;
+            f[i] = chained ? nd.op == kRSumExpShifted || nd.op == kRSumSqCentred : nd.op == EWF_RSUM || nd.op == EWF_RPROD;
+        }
+        return f;
+    }
+
+    // Copies the flagged slots of the accumulator `src` to `dst`.
+    void emit_take_slots(const std::string &dst, const std::string &src, const std::vector<int> &nodes, const std::vector<char> &slots, const std::string &ind)
+    {
+        for (size_t i = 0; i < nodes.size(); i++) {
+            if (!slots[i]) continue;
+            const int op = g.nodes[nodes[i]].op;
+            const std::string n = std::to_string(i);
+            o << ind << dst << ".a" << n << " = " << src << ".a" << n << ";";
+            if (op == kRSumExpShifted || op == kRSumSqCentred) o << " " << dst << ".b" << n << " = " << src << ".b" << n << ";";
+            if (op == kRSumSqCentred) o << " " << dst << ".n" << n << " = " << src << ".n" << n << ";";
+            o << "\n";
+        }
+    }
+
+    // A thread that holds many vectors of a row would round a sum once per element, on one chain.
+    // Instead a vector's terms are added to each other first and the vectors to four chains, which
+    // meet at the end (the single-pass accumulators, whose merge is dear, run in the four chains
+    // element by element); slots that do not round are folded directly, so what else shares the level
+    // changes nothing.  The three calls go before the loop over the vectors, around the loop over a
+    // vector's elements, and behind the loop; `chain` is the name of the chains' array.
+    struct Chains {
+        std::vector<char> terms, chained, rounded, direct;
+        bool any = false;
+    };
+    Chains chain_slots(const std::vector<int> &nodes) const
+    {
+        Chains ch;
+        ch.terms = rounded_slots(nodes, false);
+        ch.chained = rounded_slots(nodes, true);
+        ch.rounded.assign(nodes.size(), 0);
+        ch.direct.assign(nodes.size(), 0);
+        for (size_t i = 0; i < nodes.size(); i++) {
+            ch.rounded[i] = ch.terms[i] || ch.chained[i];
+            ch.direct[i] = !ch.rounded[i];
+            ch.any = ch.any || ch.rounded[i];
+        }
+        return ch;
+    }
+    void emit_chains_open(const std::string &an, const std::string &chain, const std::string &ind)
+    {
+        o << ind << an << " " << chain << "[4];\n" << ind << "_Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) " << chain << "[i_] = " << an << "_identity();\n";
+    }
+    void emit_chains_accumulate(const Chains &ch, const std::string &av, const std::string &chain, const std::string &which, const std::vector<int> &nodes,
+                                const std::function<std::string(int)> &argmax_index, const std::string &ind)
+    {
+        emit_accumulate("part_", nodes, argmax_index, ind, true, &ch.terms);
+        emit_accumulate(chain + "[" + which + " & 3]", nodes, argmax_index, ind, true, &ch.chained);
+        emit_accumulate(av, nodes, argmax_index, ind, true, &ch.direct);
+    }
+    void emit_chains_vector(const Chains &ch, const std::string &an, const std::string &chain, const std::string &which, const std::vector<int> &nodes, const std::string &ind)
+    {
+        o << ind << "{ const " << an << " sum_ = " << an << "_combine()(" << chain << "[" << which << " & 3], part_);\n";
+        emit_take_slots(chain + "[" + which + " & 3]", "sum_", nodes, ch.terms, ind + "  ");
+        o << ind << "}\n";
+    }
+    void emit_chains_close(const Chains &ch, const std::string &an, const std::string &av, const std::string &chain, const std::vector<int> &nodes, const std::string &ind)
+    {
+        o << ind << "{ const " << an << " all_ = " << an << "_combine()(" << an << "_combine()(" << chain << "[0], " << chain << "[1]), " << an << "_combine()(" << chain << "[2], " << chain << "[3]));\n";
+        emit_take_slots(av, "all_", nodes, ch.rounded, ind + "  ");
+        o << ind << "}\n";
+    }
+
     // Slots that can take a whole vector of elements at once (float32 arguments): the running
     // maximum of a sum of shifted exponentials, of a maximum and -- met in ascending order -- of an
     // arg-max.  Returns one flag per position of `nodes`.

@@ -225,12 +225,14 @@ ewf_status Gen::gen_lane()
         for (int n : lvl[l]) tg.push_back(g.nodes[n].args[0]);
         std::vector<char> need = needed(tg);
         o << "        " << an << " " << av << " = " << an << "_identity();\n";
-        // Where a lane took over the vectors of others, a vector's terms are added to each other first
-        // and the vectors to four chains: no more roundings on a path than the lanes it replaces had
-        // (sums over rows of 144 float32: relative error 6.6e-8 in one chain of 36, 4.8e-8 before).
-        bool chains = took_over && NV >= 3;
-        for (int n : lvl[l]) chains = chains && g.nodes[n].op == EWF_RSUM;
-        if (chains) o << "        " << an << " sub" << l << "_[4];\n        _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) sub" << l << "_[i_] = " << an << "_identity();\n";
+        // Where a lane took over the vectors of others, or its vectors are wider than the strict ones,
+        // sums go through chains: no more roundings on a path than the lanes it replaces had
+        // (sums over rows of 144 float32: relative error 6.6e-8 in one chain of 36, 4.8e-8 before;
+        // over 480 behind an odd element 5.4e-8 and 3.7e-8).
+        const Chains ch = chain_slots(lvl[l]);
+        const bool chains = (took_over || loose) && NV >= 3 && ch.any;
+        const std::string sub = "sub" + std::to_string(l) + "_";
+        if (chains) emit_chains_open(an, sub, "        ");
         o << "        #pragma unroll\n        for (int j = 0; j < " << NV << "; ++j) {\n";
         o << "            const int col = (j * " << L << " + lr) * EWF_VEC;\n";
         if (ragged_cols) o << "            if (col >= " << cols << ") continue;\n";
@@ -239,11 +241,13 @@ ewf_status Gen::gen_lane()
         o << skip_outside;
         emit_values(need, cx, "                ");
         // a lane walks its columns in increasing order
-        emit_accumulate(chains ? std::string("part_") : av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
+        auto index = [&](int node) { return argmax_index(node, cx.coord); };
+        if (chains) emit_chains_accumulate(ch, av, sub, "j", lvl[l], index, "                ");
+        else emit_accumulate(av, lvl[l], index, "                ", true);
         o << "            }\n";
-        if (chains) o << "            sub" << l << "_[j & 3] = " << an << "_combine()(sub" << l << "_[j & 3], part_);\n";
+        if (chains) emit_chains_vector(ch, an, sub, "j", lvl[l], "            ");
         o << "        }\n";
-        if (chains) o << "        " << av << " = " << an << "_combine()(" << an << "_combine()(sub" << l << "_[0], sub" << l << "_[1]), " << an << "_combine()(sub" << l << "_[2], sub" << l << "_[3]));\n";
+        if (chains) emit_chains_close(ch, an, av, sub, lvl[l], "        ");
         emit_first_index(av, lvl[l], "lr * EWF_VEC < " + std::to_string(cols), "lr * EWF_VEC", "        ");
         // the lanes of a row fold with a fixed butterfly; afterwards each holds the row's result
         for (int m = 1; m < L; m *= 2)

@@ -384,22 +384,26 @@ ewf_status Gen::gen_row()
         for (int n : lvl[l]) tg.push_back(g.nodes[n].args[0]);
         std::vector<char> need = needed(tg);
         o << "        " << an << " " << av << " = " << an << "_identity();\n";
+        // Sums over many vectors per thread go through chains (thirteen vectors of four for the gradient
+        // of softmax cross-entropy on rows of 50257, whose sums would otherwise round more often
+        // than those of rows split over workgroups).
+        const Chains ch = chain_slots(lvl[l]);
+        const bool chains = resident && regs > 48 && ch.any;
+        const std::string sub = "sub" + std::to_string(l) + "_";
+        if (chains) emit_chains_open(an, sub, "        ");
         open_pass();
         stream_loads(need);
-        // Sums over many vectors per thread: a vector's terms are added to each other first, so that the
-        // chain of roundings is as long as the thread has vectors, not elements (thirteen against
-        // fifty-two for the gradient of softmax cross-entropy on rows of 50257, whose sums would
-        // otherwise round more often than those of rows split over workgroups).
-        bool by_vector = resident && regs > 48;
-        for (int n : lvl[l]) by_vector = by_vector && g.nodes[n].op == EWF_RSUM;
-        if (by_vector) o << "            " << an << " part_ = " << an << "_identity();\n";
+        if (chains) o << "            " << an << " part_ = " << an << "_identity();\n";
         o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
         if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
         emit_values(need, cx, "                ");
-        emit_accumulate(by_vector ? std::string("part_") : av, lvl[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
+        auto index = [&](int node) { return argmax_index(node, cx.coord); };
+        if (chains) emit_chains_accumulate(ch, av, sub, "u", lvl[l], index, "                ");
+        else emit_accumulate(av, lvl[l], index, "                ", true);
         o << "            }\n";
-        if (by_vector) o << "            " << av << " = " << an << "_combine()(" << av << ", part_);\n";
+        if (chains) emit_chains_vector(ch, an, sub, "u", lvl[l], "            ");
         close_pass();
+        if (chains) emit_chains_close(ch, an, av, sub, lvl[l], "        ");
         // every thread walks its columns in increasing order, starting at tid * EWF_VEC
         emit_first_index(av, lvl[l], "(idx_t)tid * EWF_VEC < cols", "tid * EWF_VEC", "        ");
         // (every level has a buffer of its own: without a loop over rows it is written once)

@@ -63,3 +63,34 @@ def test_layer_normalisation_of_short_rows(storage, cols, oracle, G):
     # the subtraction of the mean cancels: relative to |x| + |mean| over the deviation, here below 8
     bar = G.h.HALF if storage == "f16" else G.h.REDUCTION
     G.h.compare("normalised", got[0], want[0], bar[0], 8 * bar[1])
+
+
+@pytest.mark.parametrize("storage,rows,cols,offset,written", [("f32", 40001, 144, 0, False), ("f16", 40001, 272, 0, False), ("f32", 40001, 480, 1, False),
+                                                              ("f16", 8197, 406, 0, True), ("f32", 4099, 301, 0, True), ("f32", 131, 49153, 0, True), ("f32", 131, 57341, 1, True)])
+def test_sums_do_not_depend_on_what_shares_their_pass(storage, rows, cols, offset, written, G):
+    """A sum and a product meet their terms in the same order, to the bit, whether or not a minimum and an
+    arg-max are taken in the same pass; rows held by few lanes and long rows in registers (those are
+    held by one workgroup only if they are written back)."""
+    rng = np.random.default_rng(cols)
+    buf = (1 + 0.01 * rng.standard_normal(rows * cols + offset)).astype(np.float16 if storage == "f16" else np.float32)
+    x = buf[offset:].reshape(rows, cols)
+    got = []
+    for extremes in (False, True):
+        s = GraphSpec(2)
+        xi = s.input(storage, (False, False))
+        total = s.reduce("sum", xi, (1,), keep=True)
+        s.output(total, "f32")
+        s.output(s.reduce("prod", xi, (1,), keep=True), "f32")
+        if written:
+            s.output(s.mul(xi, s.apply("recip", total)), storage)
+        if extremes:
+            s.output(s.reduce("min", xi, (1,)), "f32"); s.output(s.reduce("argmax", s.apply("neg", xi), (1,)), "i32")
+        print(f"[case] sum and product {storage} {rows} x {cols} + {offset}, extremes {extremes}", flush=True)
+        expr, out = run_spec(G, s, [x])
+        assert expr.info()["kernel_class"] == ("row" if cols > 4096 else "lane") and "sub1_[4]" in expr.source(), expr.info()
+        got.append(out)
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+    G.h.compare("sum", got[0][0], x.astype(np.float64).sum(1, keepdims=True).astype(np.float32), *G.h.REDUCTION)
+    np.testing.assert_array_equal(got[1][-2], x.min(1).astype(np.float32))
+    np.testing.assert_array_equal(got[1][-1], x.argmin(1).astype(np.int32))
