@@ -108,7 +108,7 @@ ewf_status generate(const Exec &e, Plan &p)
     int narrowest = 4;
     for (const Operand &op : c.ops) if (op.stride[c.rank - 1] != 0) narrowest = std::min(narrowest, op.storage == EWF_F16 ? 2 : 4);
     const bool worth = p.kclass == KernelClass::TileReduce || p.kclass == KernelClass::Row ||
-                       (p.kclass == KernelClass::Tile && c.vec * narrowest <= 2 && Gen(e, p).permuted_operand() < 0);
+                       (p.kclass == KernelClass::Tile && c.vec * narrowest <= 2 && (e.opts.no_lds_staging || Gen(e, p).permuted_operand() < 0));
     if (worth && c.vec_loose > c.vec && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
         const int strict = c.vec;
         p.canon.vec = c.vec_loose;

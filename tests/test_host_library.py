@@ -888,3 +888,14 @@ def test_copies_of_several_permuted_operands_share_the_lds(shape, order, copies,
         e.plan(ins, [ref(BASE + (100 << 32), shape)])
         info = e.info()
         assert info["kernel_class"] == "tile" and info["staged_operands"] == copies and info["lds_bytes"] <= 160 * 1024, info
+
+
+def test_unstaged_permuted_operands_keep_wide_accesses_beside_them():
+    """float16 rows of odd length, an operand read against its memory order, staging switched off: the
+    other operands and the output are still accessed in whole vectors."""
+    s = GraphSpec(2)
+    s.output(s.add(s.input("f16", (False, False)), s.input("f16", (False, False))), "f16")
+    for opts, staged in (({}, 1), ({"no_lds_staging": 1}, 0)):
+        e = ewf.Expression(s, **opts)
+        e.plan([ref(BASE, (4001, 4003)), ref(BASE + (1 << 32), (4001, 4003), (1, 4001))], [ref(BASE + (2 << 32), (4001, 4003))])
+        assert e.info()["staged_operands"] == staged and e.info()["vec"] == 8 and "ewf_st_u<" in e.source(), e.info()
