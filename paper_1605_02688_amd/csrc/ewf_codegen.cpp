@@ -115,8 +115,9 @@ ewf_status generate(const Exec &e, Plan &p)
         p.loose_vec = true;
         Gen wide(e, p);
         ewf_status st = p.kclass == KernelClass::Row ? wide.gen_row() : wide.gen_tile(p.kclass == KernelClass::TileReduce);
-        // (a row refused for its length is not held element by element instead)
-        if (st == EWF_OK || p.row_refused) return st;
+        // (a row refused for its length is not held element by element instead; what takes its place is
+        // planned with the strict width as well)
+        if (st == EWF_OK || (p.kclass == KernelClass::Row && p.row_refused)) return st;
         p.canon.vec = strict;
         p.loose_vec = false;
     }
