@@ -148,12 +148,18 @@ ewf_status generate(const Exec &e, Plan &p)
         }
     }
     // Several rows per wavefront: wide vectors at any alignment where the strict ones are single
-    // float32 elements, or float16 on rows of at least 512 bytes (softmax over float32 rows of 143 33.5 ->
-    // 28.0 us, 67 17.1 -> 14.5 us; float16 rows of 1001 56.9 -> 50.2 us; layer normalisation of float16 rows of
-    // 2324 42.0 -> 36.4 us, 1025 34.3 -> 28.0 us; the backward pass of bias + ReLU + channel sums on planes of
-    // 7 x 7 45.8 -> 38.5 us).  Short float16 rows (139 columns 7.8 against 8.6 us) and pairs of float32 (130
-    // columns 16.2 against 16.8 us) are faster as they are.
-    const bool lane_loose = narrowest == 4 ? c.vec == 1 : c.extent[c.rank - 1] * narrowest >= 512;
+    // float32 elements, or float16 on rows of at least 512 bytes that are written back.  (Softmax over float32 rows of
+    // 67 17.0 -> 14.7 us; 301, 361 MB, 81.5 -> 72.5; float16 rows of 1001 28.1 -> 25.9; layer normalisation of
+    // float16 rows of 513 26.0 -> 20.9, 2324 23.6 -> 21.4; the backward pass of bias + ReLU + channel sums on planes
+    // of 7 x 7 45.6 -> 38.2.  Float16 rows that are only read are faster as they are: sums over [40000, 480]
+    // behind an odd element 9.0 against 11.1 us, [9716, 1005] 5.7 against 6.8; so are short float16 rows -- 139 columns
+    // 7.8 against 8.6 -- and pairs of float32 -- 130 columns 16.2 against 16.8 --; and long float32 rows that are written
+    // back while both tensors fit the memory-side cache: softmax over [40000, 480] 28.8 against 30.6 us, [9716, 1005]
+    // 16.9 against 18.0, but [80000, 700] 88.5 against 86.2, [70000, 1005] 117.5 against 111.4.)
+    bool writes_rows = false;
+    for (const OutputDecl &od : e.g.outputs) writes_rows = writes_rows || (e.g.nodes[od.value].bcast & p.red.axes) != p.red.axes;
+    const int64_t cols = c.extent[c.rank - 1];
+    const bool lane_loose = narrowest == 4 ? c.vec == 1 && !(writes_rows && cols >= 448 && c.total < (int64_t)24 << 20) : writes_rows && cols * narrowest >= 512;
     if (p.kclass == KernelClass::Lane && c.vec_loose > c.vec && lane_loose && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
         // (the plan keeps reporting the width that the layout's alignment allows)
         p.loose_vec = true;

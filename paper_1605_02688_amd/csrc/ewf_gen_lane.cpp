@@ -33,6 +33,25 @@ ewf_status Gen::gen_lane()
     int L = 1;
     const int64_t nvec = ceil_div(cols, VEC);
     if (cols * min_isz > 32) while (L < 64 && L < nvec) L *= 2;
+    // (rows in flight: lanes are not given up below two workgroups a compute unit -- sum and minimum over 20000
+    // rows of 272 float16 on 4 lanes, 313 workgroups, 5.5 us, on 8 4.9; over 30000 of 67 float32 on 8, 938, 3.5 us,
+    // on 32, which four a unit would ask for, 4.3)
+    int64_t rows = 1;
+    for (int d = 0; d < R - 1; d++) rows *= c.extent[d];
+    auto fills = [&](int lanes) { return rows * lanes >= (int64_t)2 * device_cu_count() * block; };
+    bool writes_rows = false;
+    for (const OutputDecl &od : g.outputs) writes_rows = writes_rows || (g.nodes[od.value].bcast & red.axes) != red.axes;
+    int vec_regs = 0, row_operands = 0;                 // registers that one vector of every row operand takes
+    for (int k = 0; k < nin; k++)
+        if (c.ops[k].stride[in_d] != 0 && live[g.input_node[k]]) { vec_regs += (VEC * isz(c.ops[k].storage) + 3) / 4; row_operands++; }
+    const int64_t on_16 = ceil_div(nvec, (int64_t)16) * vec_regs;                     // registers of a row on 16 lanes
+    // Rows that are written back in vectors at any alignment: few lanes store short pieces of lines,
+    // and 64 that hold a vector each wait for it.  33 to 56 vectors on 16 lanes (softmax over [160000, 301]
+    // float16 on 8 / 16 / 32 / 64 lanes 43.8 / 43.9 / 47.0 / 57.6 us, layer normalisation 48.2 / 51.3 / 79.6 /
+    // 63.7, [60000, 406] 24.3 / 23.1 / 28.9 / 24.7; softmax over [160000, 255] float32 72.8 / 64.8 / 68.3 / 73.7;
+    // strict accesses 61.2, 67.3, 25.0, 73.7), more on 32 at least (softmax over [80000, 700] float16 on 8 51.5,
+    // on 32 45.4, strict 55.1; layer normalisation of [60000, 900] float16 45.2 and 42.9).
+    if (loose && writes_rows && nvec > 32 && nvec <= 56 && on_16 <= 64) L = 16;
     // more vectors than lanes (narrow vectors: an odd row length, or rows that are not aligned):
     // the lane count that leaves the fewest lane slots idle, with at most 16 vectors per lane
     // (rows of 130 float32 are 65 pairs: 64 lanes would take two trips with 63 idle slots, 8 lanes
@@ -40,36 +59,37 @@ ewf_status Gen::gen_lane()
     // (... and at most 64 registers of row data per lane: two float32 operands with rows of 784
     // are held by 32 lanes, seven vectors of each, not by 16 lanes with thirteen)
     if (nvec > 64) {
-        int vec_regs = 0;                               // registers that one vector of every row operand takes
-        for (int k = 0; k < nin; k++)
-            if (c.ops[k].stride[in_d] != 0 && live[g.input_node[k]]) vec_regs += (VEC * isz(c.ops[k].storage) + 3) / 4;
         int64_t best_waste = -1;
-        for (int l = 64; l >= 8; l /= 2) {
+        for (int l = 64; l >= (loose && writes_rows ? 32 : 8); l /= 2) {
             const int64_t nv = ceil_div(nvec, (int64_t)l), waste = nv * l - nvec;
-            if (nv > 16 || (l < 64 && nv * vec_regs > 64)) break;
+            if (nv > 16 || (l < 64 && nv * vec_regs > 64) || (loose && !writes_rows && l < 64 && !fills(l))) break;
             if (best_waste < 0 || waste < best_waste) { best_waste = waste; L = l; }
         }
     }
     // Wide vectors that leave many of those lanes idle (34 vectors of a row on 64 lanes): fewer lanes
-    // with several vectors each, at a small price per halving.  Float32 rows that are written back
-    // keep their lanes, whose stores are then whole lines.  (Sums over rows of 144 float32, 142 MB,
-    // 36.3 -> 24.6 us, 288 float16 37.7 -> 24.8 us; softmax over 272 float16 16.3 -> 13.0 us, 80 float16 21.1
-    // -> 17.3 us; but 200 float32 18.7 -> 25.1 us, 80 float32 24.6 -> 29.8 us.)
-    bool writes_rows = false;
-    for (const OutputDecl &od : g.outputs) writes_rows = writes_rows || (g.nodes[od.value].bcast & red.axes) != red.axes;
+    // with several vectors each, at a small price per halving, where rows are only read.  (Sums over
+    // rows of 144 float32, 142 MB, 36.3 -> 24.6 us, 288 float16 37.7 -> 24.8 us.  Rows that are written keep
+    // their lanes, whose stores are then whole lines: 200 float32 on few lanes 18.7 -> 25.1 us, x - mean(x) on
+    // [300000, 144] float16 31.4 -> 56.7 us, softmax over [120000, 272] float16 36.0 -> 46.6 us ...)
     const int all_lanes = L;
-    if (nvec <= 64 && VEC * min_isz >= 16 && L >= 8 && (!writes_rows || min_isz == 2)) {
-        int vec_regs = 0;
-        for (int k = 0; k < nin; k++)
-            if (c.ops[k].stride[in_d] != 0 && live[g.input_node[k]]) vec_regs += (VEC * isz(c.ops[k].storage) + 3) / 4;
+    if (nvec <= 64 && VEC * min_isz >= 16 && L >= 8 && !writes_rows) {
         double best = (double)L;
         const int top = L;
         for (int l = top / 2; l >= 4; l /= 2) {
             const int64_t nv = ceil_div(nvec, (int64_t)l);
-            if (nv * vec_regs > 48) break;
+            if (nv * vec_regs > 48 || !fills(l)) break;
             const double cost = (double)(nv * l) * (l == 4 ? 1.2 : l == 8 ? 1.1 : 1.05);
             if (cost < best) { best = cost; L = l; }
         }
+    }
+    // ... but float16 rows with chained reductions, whose folds over the lanes weigh more: lanes of two to
+    // four vectors (softmax over [160000, 272] on 64 / 16 / 4 lanes 47.6 / 38.3 / 62.5 us, layer normalisation
+    // 49.4 / 42.7 / 44.6; softmax over [160000, 144] on 32 / 16 / 4 28.7 / 21.4 / 33.1, over [160000, 80] on 16 / 8 17.1 / 13.1;
+    // layer normalisation, three rows in registers, of [160000, 200] on 32 / 16 28.6 / 37.1).
+    if (!loose && writes_rows && VEC * min_isz >= 16 && min_isz == 2 && red.max_depth >= 2) {
+        if (nvec > 32 && nvec <= 56 && on_16 <= 48) L = 16;
+        else if (row_operands == 1 && nvec > 16 && nvec <= 28) L = 16;
+        else if (row_operands == 1 && nvec > 8 && nvec <= 14) L = 8;
     }
     const bool took_over = L < all_lanes;              // a lane holds the vectors of several
     // ... but at least 16 bytes of the row per lane: where the row length or the alignment allows

@@ -899,3 +899,33 @@ def test_unstaged_permuted_operands_keep_wide_accesses_beside_them():
         e = ewf.Expression(s, **opts)
         e.plan([ref(BASE, (4001, 4003)), ref(BASE + (1 << 32), (4001, 4003), (1, 4001))], [ref(BASE + (2 << 32), (4001, 4003))])
         assert e.info()["staged_operands"] == staged and e.info()["vec"] == 8 and "ewf_st_u<" in e.source(), e.info()
+
+
+@pytest.mark.parametrize("kind,storage,rows,cols,lanes,wide", [
+    ("mean", "f16", 300000, 144, 32, False),         # rows that are written back keep their lanes ...
+    ("mean", "f16", 60000, 272, 64, False),
+    ("softmax", "f16", 60000, 272, 16, False),       # ... but for chained reductions
+    ("softmax", "f16", 60000, 80, 8, False),
+    ("sum", "f32", 100000, 144, 4, False),           # rows that are only read give them up, as long as
+    ("sum", "f16", 20000, 272, 8, False),            # two workgroups a compute unit are left
+    ("sum", "f32", 10000, 144, 16, False),
+    ("sum", "f16", 40000, 481, 64, False),           # float16 rows that are only read: strict accesses
+    ("softmax", "f16", 60000, 301, 16, True),
+    ("softmax", "f16", 60000, 701, 32, True),
+    ("softmax", "f32", 40000, 481, 64, False),       # long float32 rows that fit the memory-side cache
+    ("softmax", "f32", 80000, 481, 64, True),
+])
+def test_lanes_of_short_rows(kind, storage, rows, cols, lanes, wide):
+    s = GraphSpec(2)
+    x = s.input(storage, (False, False))
+    if kind == "sum":
+        s.output(s.reduce("sum", x, (1,)), "f32")
+    elif kind == "mean":
+        s.output(s.sub(x, s.mul(s.reduce("sum", x, (1,), keep=True), s.const(1.0 / cols))), storage)
+    else:
+        e = s.apply("exp", s.sub(x, s.reduce("max", x, (1,), keep=True)))
+        s.output(s.div(e, s.reduce("sum", e, (1,), keep=True)), storage)
+    e = ewf.Expression(s)
+    e.plan([ref(BASE, (rows, cols))], [ref(BASE + (1 << 32), (rows,) if kind == "sum" else (rows, cols))])
+    src = e.source()
+    assert e.info()["kernel_class"] == "lane" and f"const int lr = threadIdx.x & {lanes - 1};" in src and ("ewf_ld_u<" in src) == wide, src[:3000]
