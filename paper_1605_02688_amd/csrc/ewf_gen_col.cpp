@@ -63,20 +63,36 @@ ewf_status Gen::gen_col()
     // Rows per tile at which its partial results stay a thirty-second of what it moves: 128 bytes of
     // every column for a plain sum, 8 rows for the LSTM cell's backward pass (16 streams, four sums).
     const int64_t min_tile_rows = ceil_div((int64_t)32 * (int64_t)acc_bytes(level), per_element);
+    // What one merge of two lanes' partial results costs: about the instructions per column, and for
+    // the columns of a vector.
+    int fold = 0;
+    bool ranks = false;
+    for (size_t i = 0; i < level.size(); i++) {
+        if (shared_slot(level, i) >= 0) continue;
+        const int op = g.nodes[level[i]].op;
+        fold += op == kRSumSqCentred ? 20 : op == kRSumExpShifted ? 14 : op == EWF_RARGMAX ? 8 : op == EWF_RMAX || op == EWF_RMIN ? 3 : 1;
+        ranks = ranks || op == EWF_RARGMAX;
+    }
+    const int vector_fold = fold * VEC;
     // A small problem is bound by launches, not bandwidth: when one workgroup can take whole
-    // columns (a single reduced dimension, at most 192 KiB a workgroup, which a compute unit moves
-    // in about the time a second launch costs) the column strips are narrowed until there are
-    // enough workgroups, each folds its columns completely and writes the results itself -- one
-    // launch, no workspace.
+    // columns (a single reduced dimension) the column strips are narrowed until there are enough
+    // workgroups, each folds its columns completely and writes the results itself -- one launch,
+    // no workspace.  A compute unit moves about 50 bytes a nanosecond, a second launch costs two
+    // and a half microseconds, and the rows of a workgroup are a chain.  So, in KiB a workgroup: 192
+    // where the columns are short and few or a strip takes whole rows (float32 [4661, 8] 3.4 us, two
+    // launches 5.2); else 96 for a sum or two (float32 [1264, 875] 5.1 us, two launches 5.4-8; at 192
+    // float16 [3000, 500] 8.5 us, two launches 5.4), 48 where the merges are dear (arg-max and sum of
+    // float32 [400, 4000] in one launch 6.3 us, in two 9.8; but [3000, 500] 11.8 against 9.1, float16
+    // [1500, 100] 11.4 against 7.7).  The LSTM cell's backward pass, whose elements are dear too, up to 144
+    // on short columns (batch 144, hidden size 325, 108 KiB, 6.9 us, two launches 8.2; 247 and 350, 185 KiB, 10.4 and 8.4).
     int nreduced = 0;
     for (int d = 0; d < R; d++) nreduced += c.reduced[d];
     bool whole_columns = false;
-    bool chained = false;                              // an accumulator that is a chain of dependent operations per element
-    for (int n : level) chained = chained || g.nodes[n].op == kRSumSqCentred || g.nodes[n].op == kRSumExpShifted;
-    // (less where the arithmetic of a column, on one compute unit, takes longer than its bytes: the
-    // LSTM cell's backward pass, hidden size 528, batch 208: one launch 9.5 us, two 8.3 us; batch 115
-    // 6.1 us against 8.2 us)
-    const int64_t whole_bytes = (chained ? 32 : heavy >= 4 ? 96 : 192) * 1024;
+    const bool brief = small && c.extent[dR] <= 1024;
+    auto whole_bytes = [&](int tx) {
+        if (c.extent[in_d] <= (int64_t)tx * VEC && (brief || fold <= 2)) return 192 * 1024;
+        return (heavy >= 4 ? (brief ? 144 : 96) : brief ? 192 : fold <= 2 ? 96 : 48) * 1024;
+    };
     if (nreduced == 1 && e.opts.tile_elems <= 0) {
         int64_t other = 1;
         for (int d = 0; d < R - 1; d++) if (d != dR) other *= c.extent[d];
@@ -84,10 +100,10 @@ ewf_status Gen::gen_col()
         // over axis 0 in strips of 16 columns 7.1 us, two launches 5.6 us)
         int narrowest = 4;
         for (int k : swept) if (c.ops[k].stride[in_d] != 0) narrowest = std::min(narrowest, isz(c.ops[k].storage));
-        const int min_tx = small && c.extent[dR] <= 1024 ? std::max(1, 16 / VEC) : std::max(1, 64 / (VEC * narrowest));
+        const int min_tx = brief ? std::max(1, 16 / VEC) : std::max(1, 64 / (VEC * narrowest));
         int tx = TX;
-        while (tx > min_tx && (ceil_div(c.extent[in_d], (int64_t)tx * VEC) * other < 64 || c.extent[dR] * tx * VEC * per_element > whole_bytes)) tx /= 2;
-        whole_columns = c.extent[dR] * std::min<int64_t>(c.extent[in_d], (int64_t)tx * VEC) * per_element <= whole_bytes &&
+        while (tx > min_tx && (ceil_div(c.extent[in_d], (int64_t)tx * VEC) * other < 64 || c.extent[dR] * std::min<int64_t>(c.extent[in_d], (int64_t)tx * VEC) * per_element > whole_bytes(tx))) tx /= 2;
+        whole_columns = c.extent[dR] * std::min<int64_t>(c.extent[in_d], (int64_t)tx * VEC) * per_element <= whole_bytes(tx) &&
                         (small || c.total * per_element <= (int64_t)24 << 20);
         if (whole_columns) TX = tx;
     }
@@ -118,10 +134,17 @@ ewf_status Gen::gen_col()
             TZ = block / (TX * TY);
         }
     }
-    // A workgroup that takes whole columns grows until a thread has one row of them: its
-    // trips are a chain of memory latencies.
+    // A workgroup that takes whole columns grows until a thread has one row of them (its trips are a
+    // chain of memory latencies), as far as its merges are cheap: every wavefront folds its own rows
+    // first, four wavefronts to a SIMD in a workgroup of 1024, and they meet one after another.
+    // Sum of float32 [900, 300] 256 / 512 / 1024 threads 4.0 / 4.0 / 4.1 us, of float16 [300, 64], vectors of
+    // eight, 3.2 / 3.2 / 4.1; with an element-wise tanh beside it float32 [1000, 64] 7.6 / 5.9 / 5.5;
+    // arg-max and sum of float32 [300, 64] 4.8 / 5.2 / 8.0, [1000, 64] 8.0 / 6.4 / 8.8, of float16 [1000, 64] 11.1 /
+    // 9.2 / 15.5; five reductions of float32 [300, 64] 4.0 / 4.8 / 7.4; mean and variance 4.1 / 5.3 / 9.0.
+    // The LSTM cell's backward pass, batch 240, hidden size 352, 7.6 us with 512 threads, 12.3 with 1024.
+    const int most = heavy < 4 && (vector_fold <= 4 || (!ew_out_ops.empty() && vector_fold <= 8)) ? 1024 : vector_fold <= 20 || ranks ? 512 : 256;
     if (whole_columns && TZ == 1 && e.opts.block_threads <= 0) {
-        while (block < (heavy >= 4 ? 512 : 1024) && c.extent[dR] > (int64_t)(block / TX) &&
+        while (block < most && c.extent[dR] > (int64_t)(block / TX) &&
                (int64_t)(2 * block / 64 - 1) * TX * VEC * (int64_t)acc_bytes(level) <= 32 * 1024) block *= 2;
         TY = block / TX;
         p.block = block;
@@ -155,8 +178,10 @@ ewf_status Gen::gen_col()
             U = rpt;
         }
     }
+    // (with an arg-max, whose elements are a dependent chain, eight elements a trip: float16 [1000, 64]
+    // 9.2 us, with 32 elements 10.6)
     if (whole_columns && TZ == 1 && e.opts.unroll <= 0)
-        U = (int)std::max<int64_t>(1, std::min<int64_t>(ew_out_ops.empty() ? (VEC >= 4 ? 4 : 8) : heavy >= 4 ? 2 : std::max(1, 16 / VEC), ceil_div(c.extent[dR], TY)));
+        U = (int)std::max<int64_t>(1, std::min<int64_t>(ew_out_ops.empty() ? (ranks && VEC >= 4 ? 8 / VEC : VEC >= 4 ? 4 : 8) : heavy >= 4 ? 2 : std::max(1, 16 / VEC), ceil_div(c.extent[dR], TY)));
     // A kernel with element-wise outputs that would leave compute units without work takes
     // narrower strips (256 bytes of a float32 row at least): more workgroups for the same number of
     // partial results.
@@ -373,23 +398,36 @@ ewf_status Gen::gen_col()
         for (int m = TX; m < (TZ > 1 ? TX * TY : 64); m *= 2)
             o << in2 << "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], ewf_lane_xor(acc[e_], " << m << "));\n";
         if (NW > 1 && TZ == 1) {
-            o << in2 << "if (tid >= 64 && (tid & 63) < EWF_TX) { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) sm_col[(((tid >> 6) - 1) * EWF_TX + tx) * EWF_VEC + e_] = acc[e_]; }\n";
-            o << in2 << "__syncthreads();\n";
-            o << in2 << "if (tid < EWF_TX) {\n";
-            if (NW <= 4) {
-                o << in2 << "    for (int w_ = 0; w_ < EWF_NWAVES - 1; ++w_)\n";
-                o << in2 << "        _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], sm_col[(w_ * EWF_TX + tx) * EWF_VEC + e_]);\n";
+            if (NW <= 4 || vector_fold <= 20) {
+                o << in2 << "if (tid >= 64 && (tid & 63) < EWF_TX) { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) sm_col[(((tid >> 6) - 1) * EWF_TX + tx) * EWF_VEC + e_] = acc[e_]; }\n";
+                o << in2 << "__syncthreads();\n";
+                o << in2 << "if (tid < EWF_TX) {\n";
+                if (NW <= 4) {
+                    o << in2 << "    for (int w_ = 0; w_ < EWF_NWAVES - 1; ++w_)\n";
+                    o << in2 << "        _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], sm_col[(w_ * EWF_TX + tx) * EWF_VEC + e_]);\n";
+                } else {
+                    // (many wavefronts meet in a tree: a chain of fifteen sums would round more often
+                    // than the longer trips of a small workgroup did)
+                    o << in2 << "    _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
+                    o << in2 << "        Acc w_[EWF_NWAVES];\n" << in2 << "        w_[0] = acc[e_];\n";
+                    o << in2 << "        _Pragma(\"unroll\") for (int i_ = 1; i_ < EWF_NWAVES; ++i_) w_[i_] = sm_col[((i_ - 1) * EWF_TX + tx) * EWF_VEC + e_];\n";
+                    o << in2 << "        _Pragma(\"unroll\") for (int s_ = 1; s_ < EWF_NWAVES; s_ *= 2)\n";
+                    o << in2 << "            _Pragma(\"unroll\") for (int i_ = 0; i_ + s_ < EWF_NWAVES; i_ += 2 * s_) w_[i_] = Acc_combine()(w_[i_], w_[i_ + s_]);\n";
+                    o << in2 << "        acc[e_] = w_[0];\n" << in2 << "    }\n";
+                }
+                o << in2 << "}\n";
             } else {
-                // (many wavefronts meet in a tree: a chain of fifteen sums would round more often
-                // than the longer trips of a small workgroup did)
-                o << in2 << "    _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
-                o << in2 << "        Acc w_[EWF_NWAVES];\n" << in2 << "        w_[0] = acc[e_];\n";
-                o << in2 << "        _Pragma(\"unroll\") for (int i_ = 1; i_ < EWF_NWAVES; ++i_) w_[i_] = sm_col[((i_ - 1) * EWF_TX + tx) * EWF_VEC + e_];\n";
-                o << in2 << "        _Pragma(\"unroll\") for (int s_ = 1; s_ < EWF_NWAVES; s_ *= 2)\n";
-                o << in2 << "            _Pragma(\"unroll\") for (int i_ = 0; i_ + s_ < EWF_NWAVES; i_ += 2 * s_) w_[i_] = Acc_combine()(w_[i_], w_[i_ + s_]);\n";
-                o << in2 << "        acc[e_] = w_[0];\n" << in2 << "    }\n";
+                // Dear merges: the wavefronts meet pairwise, each pair in its left wavefront (which has a
+                // slot of its own for the one time it is a right one).  Arg-max and sum of float16 [300,
+                // 64] 8.2 us, all eight wavefronts merged by the first 9.3; a plain sum pays 0.4 us for
+                // the barriers.
+                o << in2 << "_Pragma(\"unroll 1\") for (int s_ = 1; s_ < EWF_NWAVES; s_ *= 2) {\n";
+                o << in2 << "    const int w_ = tid >> 6, at_ = w_ & (2 * s_ - 1);\n";
+                o << in2 << "    if (at_ == s_ && (tid & 63) < EWF_TX) { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) sm_col[((w_ - 1) * EWF_TX + tx) * EWF_VEC + e_] = acc[e_]; }\n";
+                o << in2 << "    __syncthreads();\n";
+                o << in2 << "    if (at_ == 0 && w_ + s_ < EWF_NWAVES && (tid & 63) < EWF_TX) { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], sm_col[((w_ + s_ - 1) * EWF_TX + tx) * EWF_VEC + e_]); }\n";
+                o << in2 << "}\n";
             }
-            o << in2 << "}\n";
         }
         o << in2 << "if (" << (TZ > 1 ? "ty == 0" : "tid < EWF_TX") << " && " << okname << ") {\n";
         o << in2 << "    size_t group = 0, slot = 0;\n";

@@ -60,3 +60,23 @@ def test_variance_about_a_huge_mean(shape, axes, G):
     # by up to a few of its spacings (8.8e12), four against a deviation of 3e16 change a squared
     # deviation by 2 * 4 * 8.8e12 / 3e16 = 2.3e-3 at worst.
     G.h.compare("var", got[1], x.astype(np.float64).var(axes, keepdims=True).astype(np.float32), 2.5e-3, 0)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("shape", [(300, 64), (1000, 64), (257, 20), (1024, 256), (129, 2000)])
+def test_arg_max_down_columns_of_one_workgroup(shape, storage, oracle, G):
+    """Eight wavefronts that meet pairwise: ties between them, rows that leave some without a row, NaN."""
+    dt = np.float16 if storage == "f16" else np.float32
+    rng = np.random.default_rng(shape[0])
+    x = rng.integers(-3, 4, shape).astype(dt)                   # many equal maxima: the first one counts
+    x[shape[0] // 2, 3] = np.nan
+    s = GraphSpec(2)
+    v = s.input(storage, (False, False))
+    s.output(s.reduce("argmax", v, (0,)), "i32")
+    s.output(s.reduce("sum", s.apply("abs", v), (0,)), "f32")
+    print(f"[case] arg-max {storage} {shape}", flush=True)
+    expr, got = run_spec(G, s, [x])
+    assert expr.info()["kernel_class"] == "col" and expr.info()["block_threads"] == 512 and "ewf_finish(" not in expr.source(), expr.info()
+    want = oracle.evaluate(s, [x], nthreads=4)
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_array_equal(got[1], want[1])              # small whole numbers: exact

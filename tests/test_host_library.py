@@ -929,3 +929,39 @@ def test_lanes_of_short_rows(kind, storage, rows, cols, lanes, wide):
     e.plan([ref(BASE, (rows, cols))], [ref(BASE + (1 << 32), (rows,) if kind == "sum" else (rows, cols))])
     src = e.source()
     assert e.info()["kernel_class"] == "lane" and f"const int lr = threadIdx.x & {lanes - 1};" in src and ("ewf_ld_u<" in src) == wide, src[:3000]
+
+
+def _down_columns(kind, storage, rows, cols):
+    s = GraphSpec(2)
+    x = s.input(storage, (False, False))
+    if kind == "var":
+        mean = s.mul(s.reduce("sum", x, (0,), keep=True), s.const(1.0 / rows))
+        s.output(s.mul(s.reduce("sum", s.apply("sqr", s.sub(x, mean)), (0,), keep=True), s.const(1.0 / rows)), "f32")
+    else:
+        for op in kind.split("+"):
+            s.output(s.reduce(op, x, (0,), keep=True), "i32" if op == "argmax" else "f32")
+    e = ewf.Expression(s)
+    e.plan([ref(BASE, (rows, cols))], [ref(BASE + ((k + 1) << 32), (1, cols)) for k in range(e.n_outputs)])
+    return e
+
+
+@pytest.mark.parametrize("kind,storage,rows,cols,threads", [
+    ("sum", "f32", 900, 300, 1024), ("sum", "f16", 300, 64, 512), ("sum+argmax", "f32", 1000, 64, 512), ("sum+argmax", "f16", 300, 64, 512),
+    ("sum+max+min+prod", "f32", 300, 64, 256), ("var", "f32", 256, 512, 256), ("var", "f16", 1000, 64, 256),
+    ("var", "f32", 400, 2000, 256), ("sum", "f32", 4661, 8, 1024), ("sum", "f32", 1264, 875, 1024),       # one launch ...
+    ("sum", "f16", 3000, 500, None), ("sum+argmax", "f16", 1500, 100, None), ("sum+argmax", "f32", 3000, 40, None), ("var", "f32", 2000, 64, None),
+])
+def test_columns_in_one_launch_and_in_two(kind, storage, rows, cols, threads):
+    """Workgroups that take whole columns grow as far as their merges are cheap; columns whose one
+    workgroup would take longer than a second launch get two (`threads` None)."""
+    e = _down_columns(kind, storage, rows, cols)
+    multi = e.info()["kernel_class"] == "multi"                 # a variance: one stage
+    info, src = (e.info(0), e.source(0)) if multi else (e.info(), e.source())
+    assert info["kernel_class"] == "col" and ("ewf_finish(" in src) == (threads is None), info
+    assert threads is None or info["block_threads"] == threads, info
+
+
+@pytest.mark.parametrize("batch,hidden,launches", [(115, 464, 1), (144, 325, 1), (176, 1824, 1), (244, 16, 1), (247, 350, 2), (416, 784, 2)])
+def test_lstm_backward_in_one_launch_and_in_two(batch, hidden, launches):
+    e = plan_workload(wl.layout_only(wl.c2_lstm_cell_backward, batch=batch, hidden=hidden))[0]
+    assert e.info()["kernel_class"] == "col" and 1 + ("ewf_finish(" in e.source()) == launches, e.info()
