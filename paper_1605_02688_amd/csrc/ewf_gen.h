@@ -520,11 +520,12 @@ struct Gen {
     }
 
     // A thread that holds many vectors of a row would round a sum once per element, on one chain.
-    // Instead a vector's terms are added to each other first and the vectors to four chains, which
-    // meet at the end (the single-pass accumulators, whose merge is dear, run in the four chains
-    // element by element); slots that do not round are folded directly, so what else shares the level
-    // changes nothing.  The three calls go before the loop over the vectors, around the loop over a
-    // vector's elements, and behind the loop; `chain` is the name of the chains' array.
+    // Instead a vector's terms are added to each other first (in `part_`) and the vectors to a chain, of
+    // which there may be four that meet at the end (the single-pass accumulators, whose merge is dear,
+    // run in the chains element by element); slots that do not round are folded into `av` directly, so
+    // what else shares the level changes nothing.  The calls go before the loop over the vectors, inside
+    // the loop over a vector's elements, behind that, and behind the loop; `chain` is the array of four,
+    // `at` the chain of a vector.
     struct Chains {
         std::vector<char> terms, chained, rounded, direct;
         bool any = false;
@@ -547,17 +548,17 @@ struct Gen {
     {
         o << ind << an << " " << chain << "[4];\n" << ind << "_Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) " << chain << "[i_] = " << an << "_identity();\n";
     }
-    void emit_chains_accumulate(const Chains &ch, const std::string &av, const std::string &chain, const std::string &which, const std::vector<int> &nodes,
+    void emit_chains_accumulate(const Chains &ch, const std::string &av, const std::string &at, const std::vector<int> &nodes,
                                 const std::function<std::string(int)> &argmax_index, const std::string &ind)
     {
         emit_accumulate("part_", nodes, argmax_index, ind, true, &ch.terms);
-        emit_accumulate(chain + "[" + which + " & 3]", nodes, argmax_index, ind, true, &ch.chained);
+        emit_accumulate(at, nodes, argmax_index, ind, true, &ch.chained);
         emit_accumulate(av, nodes, argmax_index, ind, true, &ch.direct);
     }
-    void emit_chains_vector(const Chains &ch, const std::string &an, const std::string &chain, const std::string &which, const std::vector<int> &nodes, const std::string &ind)
+    void emit_chains_vector(const Chains &ch, const std::string &an, const std::string &at, const std::vector<int> &nodes, const std::string &ind)
     {
-        o << ind << "{ const " << an << " sum_ = " << an << "_combine()(" << chain << "[" << which << " & 3], part_);\n";
-        emit_take_slots(chain + "[" + which + " & 3]", "sum_", nodes, ch.terms, ind + "  ");
+        o << ind << "{ const " << an << " sum_ = " << an << "_combine()(" << at << ", part_);\n";
+        emit_take_slots(at, "sum_", nodes, ch.terms, ind + "  ");
         o << ind << "}\n";
     }
     void emit_chains_close(const Chains &ch, const std::string &an, const std::string &av, const std::string &chain, const std::vector<int> &nodes, const std::string &ind)

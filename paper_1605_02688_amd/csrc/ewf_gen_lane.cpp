@@ -262,10 +262,10 @@ ewf_status Gen::gen_lane()
         emit_values(need, cx, "                ");
         // a lane walks its columns in increasing order
         auto index = [&](int node) { return argmax_index(node, cx.coord); };
-        if (chains) emit_chains_accumulate(ch, av, sub, "j", lvl[l], index, "                ");
+        if (chains) emit_chains_accumulate(ch, av, sub + "[j & 3]", lvl[l], index, "                ");
         else emit_accumulate(av, lvl[l], index, "                ", true);
         o << "            }\n";
-        if (chains) emit_chains_vector(ch, an, sub, "j", lvl[l], "            ");
+        if (chains) emit_chains_vector(ch, an, sub + "[j & 3]", lvl[l], "            ");
         o << "        }\n";
         if (chains) emit_chains_close(ch, an, av, sub, lvl[l], "        ");
         emit_first_index(av, lvl[l], "lr * EWF_VEC < " + std::to_string(cols), "lr * EWF_VEC", "        ");

@@ -26,7 +26,10 @@ def test_softmax_sum_and_argmax_of_short_rows(storage, cols, oracle, G):
     s.output(s.reduce("argmax", xi, (1,)), "i32")
     print(f"[case] softmax {storage} {rows} x {cols}", flush=True)
     expr, got = run_spec(G, s, [x])
-    assert expr.info()["kernel_class"] == "lane", expr.info()
+    # wide accesses at any alignment: single float32 elements unless the rows are long and fit the
+    # memory-side cache, float16 rows of 512 bytes and more (those that are only read keep their width)
+    wide = cols % 2 == 1 and cols < 448 if storage == "f32" else cols % 8 != 0 and cols >= 256
+    assert expr.info()["kernel_class"] == "lane" and ("ewf_ld_u<" in expr.source()) == wide, expr.info()
     want = oracle.evaluate(s, [x], nthreads=8)
     bar = G.h.HALF if storage == "f16" else G.h.REDUCTION
     G.h.compare("p", got[0], want[0], *bar)
@@ -38,9 +41,23 @@ def test_softmax_sum_and_argmax_of_short_rows(storage, cols, oracle, G):
     s.output(s.reduce("min", xi, (1,)), "f32")
     x[5] = 1.0
     expr, got = run_spec(G, s, [x])
+    assert ("ewf_ld_u<" in expr.source()) == (storage == "f32" and cols % 2 == 1), expr.info()
     want = oracle.evaluate(s, [x], nthreads=8)
     G.h.compare("sum", got[0], want[0], *G.h.REDUCTION)          # terms of one sign
     G.h.compare("min", got[1], want[1], 0, 0)
+
+
+def test_softmax_of_long_odd_rows_beyond_the_memory_side_cache(oracle, G):
+    rows, cols = 25200, 1001
+    x = (np.random.default_rng(1).standard_normal((rows, cols)) * 2).astype(np.float32)
+    s = GraphSpec(2)
+    xi = s.input("f32", (False, False))
+    e = s.apply("exp", s.sub(xi, s.reduce("max", xi, (1,), keep=True)))
+    s.output(s.div(e, s.reduce("sum", e, (1,), keep=True)), "f32")
+    print(f"[case] softmax f32 {rows} x {cols}", flush=True)
+    expr, got = run_spec(G, s, [x])
+    assert expr.info()["kernel_class"] == "lane" and "ewf_ld_u<float, EWF_VEC>" in expr.source(), expr.info()
+    G.h.compare("p", got[0], oracle.evaluate(s, [x], nthreads=8)[0], *G.h.REDUCTION)
 
 
 @pytest.mark.parametrize("storage,cols", [("f16", 160), ("f16", 221), ("f16", 272), ("f16", 1025), ("f32", 144), ("f32", 179), ("f32", 749)])
@@ -87,7 +104,7 @@ def test_sums_do_not_depend_on_what_shares_their_pass(storage, rows, cols, offse
             s.output(s.reduce("min", xi, (1,)), "f32"); s.output(s.reduce("argmax", s.apply("neg", xi), (1,)), "i32")
         print(f"[case] sum and product {storage} {rows} x {cols} + {offset}, extremes {extremes}", flush=True)
         expr, out = run_spec(G, s, [x])
-        assert expr.info()["kernel_class"] == ("row" if cols > 4096 else "lane") and "sub1_[4]" in expr.source(), expr.info()
+        assert expr.info()["kernel_class"] == ("row" if cols > 4096 else "lane") and ("part_" if cols > 4096 else "sub1_[4]") in expr.source(), expr.info()
         got.append(out)
     np.testing.assert_array_equal(got[0][0], got[1][0])
     np.testing.assert_array_equal(got[0][1], got[1][1])
