@@ -280,7 +280,9 @@ typedef struct {
     int32_t rank;             /* canonical rank after dropping/merging dimensions            */
     int64_t extent[EWF_MAX_DIMS];
     int32_t reduced[EWF_MAX_DIMS];  /* 1 if the canonical dimension is reduced                */
-    int32_t vec;              /* elements per memory access along the innermost dimension    */
+    int32_t vec;              /* elements per memory access along the innermost dimension; for
+                                 kernels that hold several rows per wavefront the width that the
+                                 layout's alignment allows, whatever they use                 */
     int32_t index_bits;       /* 32 or 64                                                    */
     int32_t noperands;        /* inputs then outputs                                         */
     int32_t block_threads;

@@ -10,7 +10,7 @@ namespace ewf {
 // innermost reduced dimension are spread over the wavefronts of the workgroup (and over
 // several workgroups, "slots", when there are few columns); the per-wavefront results meet in
 // LDS in a fixed order, one partial per column and slot goes to the workspace, and a second
-// kernel folds the slots of each column in slot order.
+// kernel folds the slots of each column in a fixed order.
 
 ewf_status Gen::gen_col()
 {
@@ -183,8 +183,8 @@ ewf_status Gen::gen_col()
     if (whole_columns && TZ == 1 && e.opts.unroll <= 0)
         U = (int)std::max<int64_t>(1, std::min<int64_t>(ew_out_ops.empty() ? (ranks && VEC >= 4 ? 8 / VEC : VEC >= 4 ? 4 : 8) : heavy >= 4 ? 2 : std::max(1, 16 / VEC), ceil_div(c.extent[dR], TY)));
     // A kernel with element-wise outputs that would leave compute units without work takes
-    // narrower strips (256 bytes of a float32 row at least): more workgroups for the same number of
-    // partial results.
+    // narrower strips (sixteen lanes at least: 256 bytes of a float32 row in vectors of four, 64 in
+    // single elements): more workgroups for the same number of partial results.
     if (!whole_columns && TZ == 1 && !ew_out_ops.empty() && e.opts.tile_elems <= 0 && e.opts.unroll <= 0) {
         int64_t other = 1;
         for (int d = 0; d < R - 1; d++) if (d != dR) other *= c.extent[d];
@@ -392,8 +392,7 @@ ewf_status Gen::gen_col()
         o << in2 << "}\n";
     };
     // The row groups inside a wavefront (lanes that differ by a multiple of TX) fold with lane
-    // exchanges in a fixed butterfly; the wavefronts then meet in LDS and the first folds them
-    // in order.  Then the tile's partial results (or, with one tile per column, the results) go out.
+    // exchanges in a fixed butterfly; the wavefronts then meet in LDS, in a fixed order.  Then the tile's partial results (or, with one tile per column, the results) go out.
     auto emit_fold_and_write = [&](const std::string &in2) {
         for (int m = TX; m < (TZ > 1 ? TX * TY : 64); m *= 2)
             o << in2 << "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_combine()(acc[e_], ewf_lane_xor(acc[e_], " << m << "));\n";
@@ -526,7 +525,8 @@ ewf_status Gen::gen_col()
     o << "    }\n}\n";
 
     // ---- second kernel.  Many slots per column: the partials of a column are contiguous and a
-    // workgroup's lanes walk them.  Few: one thread per column folds its slots in slot order.
+    // workgroup's lanes walk them.  Few: one thread per column folds its slots, in four chains (slot
+    // s in chain s mod 4, what is left over in the first) that meet at the end.
     if (one_tile) { /* no second kernel */ }
     else if (fin_lanes) emit_finish_lanes(level, group_out_ops, "p.nslots", fin_block,
                                      (int)std::min<int64_t>(8, std::max<int64_t>(1, ceil_div(nslots, fin_block))));

@@ -212,9 +212,10 @@ struct Plan {
     int64_t tile[kMaxDims] = {0};
     size_t workspace_bytes = 0;
     bool empty = false;                  // zero-size iteration space: nothing to traverse
-    // The kernel was generated for canon.vec_loose: rows may start at any element and end inside
-    // a vector.  Whole vectors are read and written with accesses that assume element alignment
-    // only, the last vector of a row moved into place.
+    // The kernel was generated for vectors wider than the layout's alignment allows (canon.vec_loose at
+    // most; canon.vec says how wide, except for the lane class, whose plan keeps the strict width):
+    // rows may start at any element and end inside a vector.  Whole vectors are read and written with
+    // accesses that assume element alignment only, the last vector of a row moved into place.
     bool loose_vec = false;
     int strict_vec = 0;                  // canon.vec as the canonicaliser set it (0: not recorded yet)
     struct Fill { int output; int rank; int elem_bytes; uint32_t bits; };

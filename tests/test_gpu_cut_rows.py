@@ -59,6 +59,7 @@ def test_rows_cut_inside_a_vector(storage, cut, streaming, oracle, G):
         a, b = s.input(storage, (False, False)), s.input(storage, (True, False))
         s.output(s.add(s.mul(a, b), s.const(0.25)), storage)
         expr, got = run_spec(G, s, [x, gb[0]], streaming=streaming)
+        assert expr.info()["kernel_class"] == "tile" and ("ewf_ld_u<" in expr.source()) == (storage == "f16" and cut % 2 == 1), expr.info()
         want = oracle.evaluate(s, [x, gb[0]], nthreads=2)
         G.h.compare("scaled", got[0], want[0], *(G.h.HALF if storage == "f16" else G.h.ELEMENTWISE))
         s = GraphSpec(2)
@@ -70,6 +71,7 @@ def test_rows_cut_inside_a_vector(storage, cut, streaming, oracle, G):
         # views with different pitches, so that the two dimensions stay apart
         wide = np.zeros((rows, cols + 3), dt); wide[:, 1:1 + cols] = y
         expr, got = run_spec(G, s, [wide[:, 1:1 + cols], y], streaming=streaming)
+        assert expr.info()["kernel_class"] == "tile_reduce" and expr.info()["vec"] == vec and "ewf_ld_u<" in expr.source(), expr.info()
         want = oracle.evaluate(s, [wide[:, 1:1 + cols], y], nthreads=2)
         G.h.compare("product", got[0], want[0], *G.h.ELEMENTWISE)
         G.h.compare("sum", got[1], want[1], *G.h.REDUCTION)       # squares: terms of one sign
