@@ -125,8 +125,16 @@ ewf_status generate(const Exec &e, Plan &p)
     // accesses are read, evaluated and written in wider vectors too.  A row's last vector then
     // works on elements past the row's end, so the width is the one that costs the fewest
     // instructions: a vector costs its address arithmetic and accesses whatever it holds, an
-    // element the expression.
-    if (p.kclass == KernelClass::Tile && c.vec_loose > c.vec && !e.opts.force_scalar && !e.opts.no_lds_staging) {
+    // element the expression.  That holds for float16 with much arithmetic (four tanh on [250, 500, 64, 3] 62.6 us in
+    // single elements, 50.6 in vectors).  Otherwise accesses of eight bytes stream as they are ([64, 256, 28, 28]
+    // float16 15.5 us, 21.3 in wider vectors), and short rows are mostly cut vectors (the sum of a tensor [100, 500, 64, 9]
+    // and a permuted one, float16 35.7 and 46.6 us; [40, 500, 64, 13] float32 34.6 and 40.6; but [100, 125, 64, 31]
+    // float16 99 and 61, [32, 192, 35, 35] float16 108 and 24, float32 36.4 and 24.3).
+    int arithmetic = 0;
+    for (const Node &n : e.g.nodes) arithmetic += instructions_of(n) >= 4;
+    const int strict_bytes = c.vec * narrowest;
+    const bool long_rows = (narrowest == 2 && arithmetic >= 4) || (strict_bytes <= 4 && c.extent[c.rank - 1] >= (strict_bytes == 2 ? 28 : 32));
+    if (p.kclass == KernelClass::Tile && c.vec_loose > c.vec && long_rows && !e.opts.force_scalar && !e.opts.no_lds_staging) {
         const Gen probe(e, p);
         if (probe.permuted_operand() >= 0) {
             const int strict = c.vec;

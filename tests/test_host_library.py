@@ -965,3 +965,20 @@ def test_columns_in_one_launch_and_in_two(kind, storage, rows, cols, threads):
 def test_lstm_backward_in_one_launch_and_in_two(batch, hidden, launches):
     e = plan_workload(wl.layout_only(wl.c2_lstm_cell_backward, batch=batch, hidden=hidden))[0]
     assert e.info()["kernel_class"] == "col" and 1 + ("ewf_finish(" in e.source()) == launches, e.info()
+
+
+@pytest.mark.parametrize("storage,shape,order,vec", [
+    ("f16", (100, 500, 64, 9), (0, 1, 3, 2), 1), ("f32", (40, 500, 64, 13), (0, 1, 3, 2), 1),            # short odd rows: single elements
+    ("f16", (100, 125, 64, 31), (0, 3, 1, 2), 8), ("f16", (32, 192, 35, 35), (0, 2, 3, 1), 8), ("f32", (32, 192, 35, 35), (0, 2, 3, 1), 4),
+    ("f16", (64, 256, 28, 28), (0, 1, 3, 2), 4),                                                         # eight bytes are wide enough
+    ("f16", (4001, 4003), (1, 0), 8), ("f32", (4001, 4003), (1, 0), 4),
+])
+def test_widths_of_staged_rows_with_little_arithmetic(storage, shape, order, vec):
+    strides, acc = [0] * len(shape), 1
+    for d in reversed(order):
+        strides[d], acc = acc, acc * shape[d]
+    s = GraphSpec(len(shape))
+    s.output(s.add(s.input(storage, (False,) * len(shape)), s.input(storage, (False,) * len(shape))), storage)
+    e = ewf.Expression(s)
+    e.plan([ref(BASE, shape), ref(BASE + (1 << 32), shape, strides)], [ref(BASE + (2 << 32), shape)])
+    assert e.info()["staged_operands"] == 1 and e.info()["vec"] == vec, e.info()
