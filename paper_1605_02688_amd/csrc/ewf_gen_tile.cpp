@@ -174,10 +174,18 @@ ewf_status Gen::gen_tile(bool with_reduce)
         // 44.6 us, in 80 3.3 us; [43, 96, 27, 72] in 344 tiles 28.6, in 1032 19.5 us).  With
         // little arithmetic to spread, full tiles for half the compute units stream as well or
         // better (x + y^T on float32 [64, 100000] in 392 tiles 16.3 us, in 1042 19.2 us; [8, 512, 512] in
-        // 128 6.0, in 512 6.8 us; but [1024, 1024] in 64 5.3, in 512 4.1 us).
+        // 128 6.0, in 512 6.8 us; but [1024, 1024] in 64 5.3, in 512 4.1 us).  So do, with much arithmetic,
+        // full tiles for one and a half rounds of the compute units where rows are aligned and planes whole cache lines (the
+        // stress expression reading A on [32, 256, 56, 56] 48.4 us, four tiles a unit 55.9; [16, 64, 112, 112] 24.8
+        // and 32.1; reading B on [24, 256, 56, 56] 35.7 and 39.5; but A on [42, 173, 59, 37] 51.4 and 47.5, on [40, 512, 28, 28]
+        // 40.6 and 36.2).
         const int64_t full_tile = 65536 / szS;
+        int64_t lines = szS;                           // bytes of the shortest run of trailing dimensions that has 512
+        for (int d = R - 1; d >= 0 && lines < 512; d--) lines *= c.extent[d];
+        const bool stream_full = heavy < 4 ? c.total >= device_cu_count() / 2 * full_tile
+                                           : !loose && c.extent[R - 1] >= 16 && lines % 128 == 0 && c.total * 2 >= (int64_t)3 * device_cu_count() * full_tile;
         budget = e.opts.tile_elems > 0 ? e.opts.tile_elems
-                 : heavy < 4 && c.total >= device_cu_count() / 2 * full_tile ? full_tile
+                 : stream_full ? full_tile
                  : std::min(full_tile, std::max<int64_t>(2048, c.total / ((int64_t)4 * device_cu_count())));
         if (stage_cap > 0) budget = std::min(budget, stage_cap);
         for (int d = 0; d < kMaxDims; d++) T[d] = 1;
@@ -186,23 +194,29 @@ ewf_status Gen::gen_tile(bool with_reduce)
         // share lines on both sides, and longer runs of the operands that are not staged, of
         // which there are more, count for more (reading "A" of the float16 stress workload,
         // [43, 96, 27, 72] 23.6 -> 19.6 us, [48, 160, 14, 14] 7.7 -> 6.6 us; planes of 56 x 56, whole
-        // lines, 89.8 -> 115.8 us).
+        // lines, 89.8 -> 115.8 us).  Not for 4-byte operands, and with little arithmetic not in full tiles,
+        // whose runs are long enough on both sides (x + y permuted like A, [64, 256, 28, 28] float32 33.3 us, 38.2 with
+        // runs of 64 bytes; [32, 256, 56, 57] float16 37.3 and 43.4; x + y^T on float16 [4001, 4003] 23.2 and 29.5,
+        // but on [2000, 2001], small tiles, 12.1 and 9.8).
         int64_t plane = 1;
         for (int d = R - 1; d > sdims[0]; d--) plane *= c.extent[d];
         const bool split_lines = plane * szS >= 512 && plane * szS <= 8192 && (plane * szS % 128 != 0 || budget < 65536 / szS);
-        int64_t need_run = (split_lines ? 64 : 128) / szS;
+        int64_t need_run = (split_lines && szS == 2 && (heavy >= 4 || budget < full_tile) ? 64 : 128) / szS;
+        int64_t below = 1;                             // elements of the dimensions that are faster in the operand
         for (size_t i = 0; i < sdims.size() && need_run > 1; i++) {
             int d = sdims[i];
             T[d] = std::min<int64_t>(c.extent[d], need_run);
             if (T[d] < c.extent[d] && c.extent[d] % T[d]) {
                 // even shares: 97 channels as 33 + 33 + 31, not 32 + 32 + 32 + 1 (whole pieces where
-                // the extent is made of them)
-                const int64_t n = std::max<int64_t>(1, (c.extent[d] + T[d] / 2) / T[d]), whole = c.extent[d] % (16 / szS) == 0 ? 16 / szS : 1;
+                // the extent is made of them, as long as that leaves runs of 32 bytes along the output's
+                // order: the stress expression reading B on [3, 304, 31, 61] in tiles of (8, 31, 8) 14.8 us)
+                const int64_t n = std::max<int64_t>(1, (c.extent[d] + T[d] / 2) / T[d]), whole = c.extent[d] % (16 / szS) == 0 && (i == 0 || below * (16 / szS) * (32 / szS) <= budget) ? 16 / szS : 1;
                 T[d] = std::min(c.extent[d], ceil_div(ceil_div(c.extent[d], n), whole) * whole);
             }
             if (T[d] < c.extent[d]) break;
             if (i + 1 < sdims.size() && S.stride[sdims[i + 1]] != S.stride[d] * c.extent[d]) break;
             need_run = ceil_div(need_run, T[d]);
+            below *= T[d];
         }
         // then the longest runs along the output's order that the LDS budget allows
         for (int d = R - 1; d >= 0; d--) {

@@ -982,3 +982,13 @@ def test_widths_of_staged_rows_with_little_arithmetic(storage, shape, order, vec
     e = ewf.Expression(s)
     e.plan([ref(BASE, shape), ref(BASE + (1 << 32), shape, strides)], [ref(BASE + (2 << 32), shape)])
     assert e.info()["staged_operands"] == 1 and e.info()["vec"] == vec, e.info()
+
+
+@pytest.mark.parametrize("reading,shape,tile", [
+    ("A", (64, 256, 56, 56), 64 * 448), ("A", (32, 256, 56, 56), 64 * 448), ("B", (24, 256, 56, 56), 8 * 56 * 56),    # whole lines, enough full tiles
+    ("A", (10, 256, 56, 56), 32 * 224), ("A", (40, 512, 28, 28), 32 * 448), ("B", (3, 304, 31, 61), 4 * 31 * 16),      # else about four a compute unit
+])
+def test_tiles_of_the_stress_expression(reading, shape, tile):
+    n, c, h, w = shape
+    e = plan_workload(wl.layout_only(wl.c5_stress, n=n, c=c, h=h, w=w, reading=reading))[0]
+    assert e.info()["kernel_class"] == "tile" and e.info()["staged_operands"] == 1 and int(np.prod(e.info()["tile"])) == tile, e.info()
