@@ -143,8 +143,12 @@ ewf_status Gen::gen_col()
     // 9.2 / 15.5; five reductions of float32 [300, 64] 4.0 / 4.8 / 7.4; mean and variance 4.1 / 5.3 / 9.0.
     // The LSTM cell's backward pass, batch 240, hidden size 352, 7.6 us with 512 threads, 12.3 with 1024.
     const int most = heavy < 4 && (vector_fold <= 4 || (!ew_out_ops.empty() && vector_fold <= 8)) ? 1024 : vector_fold <= 20 || ranks ? 512 : 256;
+    // (nor beyond 512 threads a compute unit in all: sums over axis 1 of float16 [96, 35, 2411], 3648
+    // workgroups, 8.4 us with 256 threads and 15.9 with 1024, of float32 [200, 64, 300], 400, 6.4 with 512 and 7.3)
+    int64_t workgroups = ceil_div(c.extent[in_d], (int64_t)TX * VEC);
+    for (int d = 0; d < R - 1; d++) if (d != dR) workgroups *= c.extent[d];
     if (whole_columns && TZ == 1 && e.opts.block_threads <= 0) {
-        while (block < most && c.extent[dR] > (int64_t)(block / TX) &&
+        while (block < most && c.extent[dR] > (int64_t)(block / TX) && workgroups * block < (int64_t)512 * device_cu_count() &&
                (int64_t)(2 * block / 64 - 1) * TX * VEC * (int64_t)acc_bytes(level) <= 32 * 1024) block *= 2;
         TY = block / TX;
         p.block = block;

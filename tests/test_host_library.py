@@ -961,6 +961,15 @@ def test_columns_in_one_launch_and_in_two(kind, storage, rows, cols, threads):
     assert threads is None or info["block_threads"] == threads, info
 
 
+@pytest.mark.parametrize("storage,shape,threads", [("f16", (96, 35, 2411), 256), ("f32", (88, 17, 2032), 256), ("f32", (200, 64, 300), 512), ("f32", (64, 512, 60), 1024)])
+def test_many_workgroups_of_whole_columns_stay_small(storage, shape, threads):
+    s = GraphSpec(3)
+    s.output(s.reduce("sum", s.input(storage, (False,) * 3), (1,)), "f32")
+    e = ewf.Expression(s)
+    e.plan([ref(BASE, shape)], [ref(BASE + (1 << 32), (shape[0], shape[2]))])
+    assert e.info()["kernel_class"] == "col" and "ewf_finish(" not in e.source() and e.info()["block_threads"] == threads, e.info()
+
+
 @pytest.mark.parametrize("batch,hidden,launches", [(115, 464, 1), (144, 325, 1), (176, 1824, 1), (244, 16, 1), (247, 350, 2), (416, 784, 2)])
 def test_lstm_backward_in_one_launch_and_in_two(batch, hidden, launches):
     e = plan_workload(wl.layout_only(wl.c2_lstm_cell_backward, batch=batch, hidden=hidden))[0]
