@@ -75,9 +75,41 @@ ewf_status Gen::gen_row()
     int regs = 0;
     for (int k : row_ops) if (!late[k]) regs += (int)NV * VEC * isz(c.ops[k].storage) / 4;
     const bool resident = NV <= 32 && regs <= 96;
+    int64_t nrows = 1;
+    for (int d = 0; d < R - 1; d++) nrows *= c.extent[d];
+    // one workgroup per row when the grid can hold them all: no loop, so nothing is hoisted
+    // out of it into registers that the row needs
+    if (nrows >= ((int64_t)1 << 31) - 1) return fail("too many rows");
+    const int64_t grid_cap = e.opts.max_blocks > 0 ? e.opts.max_blocks : (int64_t)256 * 32;
+    const bool row_loop = nrows > grid_cap;
+    // The first NFULL steps of a resident row are in range for every thread of the
+    // workgroup at this plan's row length: straight-line code there lets the compiler wait
+    // for the loads one by one instead of for all of them.  (The row length is part of the
+    // plan's key, and NFULL of the generated text, so the assumption travels with the code.)
+    const int64_t NFULL = resident ? cols / per_iter : 0;
+    // Two workgroups of 1024 threads share a compute unit, one loading while the other computes or stores, when
+    // neither takes more than 64 registers a thread.  Left alone the compiler takes up to 128 under 52 registers of
+    // row: it keeps for the next pass what one pass computed (the exponentials, the column numbers).  In a `tight` row
+    // every pass starts from the row alone, and rows of more than 44 registers leave some of their vectors in
+    // LDS, at most 64 KiB a workgroup, read there past the registers.  Gradient of softmax cross-entropy, float32:
+    // [1280, 50257] 107.7 -> 102.4 us, [1280, 32768] 64.0 -> 60.8, [900, 61001] 120.9 -> 89.7 (two passes before), [1220, 65536]
+    // 148.4 -> 121.0; softmax over float16 [800, 100000] 183.7 -> 81.  Only where it takes less than 65 registers and the kernel
+    // left alone takes more (softmax over float32 [1000, 40000] 56.0 us left alone, 57.7 tight), not beside operands that the last
+    // pass loads, which want registers of their own (layer normalisation of float32 [1024, 65536] 101.6 us, 111.3
+    // tight), and not under a single reduction of float16 (x - mean(x) on [300, 100000] 25.2 us, 26.4 tight).
+    auto parkable = [&](int k) { return !late[k] && c.ops[k].access == Access::Vector && VEC * isz(c.ops[k].storage) == 16; };
+    const bool words = std::all_of(row_ops.begin(), row_ops.end(), [&](int k) { return isz(c.ops[k].storage) == 4; });
+    p.tight_possible = resident && !row_loop && block == 1024 && regs > 20 && std::find(late.begin(), late.end(), (char)1) == late.end() &&
+                       (words || D >= 2) && !p.no_tight;
+    p.tight_needed = false;
+    int64_t park = 0;                                  // steps of the row that wait in LDS
+    if (p.tight_possible && regs > 44) {
+        const int64_t nops = std::count_if(row_ops.begin(), row_ops.end(), parkable);
+        if (nops > 0) park = std::min({ceil_div(regs - 44, 4 * nops), NFULL, 65536 / (nops * block * 16)});
+        if (regs - 4 * nops * park > 48) { p.tight_possible = false; park = 0; }
+    }
+    const bool tight_possible = p.tight_possible, tight = p.tight && tight_possible;
     if (p.avoid_poor_rows && e.opts.split_rows != 2) {
-        int64_t nr = 1;
-        for (int d = 0; d < R - 1; d++) nr *= c.extent[d];
         // measured on [rows, cols] float32 softmax cross-entropy of 268 MB: rows held in registers
         // run at 5.3-5.5 TB/s up to 32768 columns but 4.1 TB/s at 65536 (64 registers per thread,
         // 1024 threads: one workgroup per compute unit), rows streamed once per level 2.7-3.4 TB/s;
@@ -85,23 +117,30 @@ ewf_status Gen::gen_row()
         // (a chain that a plan in passes cannot shorten -- layer normalisation of float32
         // [4096, 16384] with its scale and shift rows: 96 registers of row data, 91 us here against
         // 185 us in three passes -- keeps the row class as long as the row fits at all)
-        // (without outputs that vary along the row, from 28 registers of 1024 threads on: softmax cross-entropy on
-        // float32 [1280, 32768] 40.0 us with 1024 threads a row -- two workgroups per compute unit,
-        // two and a half rounds of them -- against 35.6 us split; [3000, 32768] 84.1 against 78.1 us,
-        // [1280, 49152] 54.6 against 49.9 us, [20000, 32768] 450 against 411 us; [1300, 24600] 35.8 against 30.8 us, [2800, 28000] 67.4 against 64.0 us,
-        // [2500, 32000] 65.4 against 65.6 us; [512, 40000] 22.1 against 23.3 us)
+        // (rows that are only read: up to 27 registers of 1024 threads; float32 sums and extremes, tight, up to 44 where there are two for
+        // each compute unit and up to 60 where there are four.  Softmax cross-entropy on float32, split over workgroups against one
+        // workgroup a row: [600, 24577] 18.6 and 15.7 us, [1220, 24577] 29.5 and 23.9, [600, 40000] 24.6 and 21.4, [1220, 32768]
+        // 33.4 and 29.2; 52 registers, [1220, 53001] 51.2 and 48.2, [600, 53001] 28.9 and 29.7; 64, [1220, 65536] 58.0 and 71.9.  From 256 MB on
+        // they stay split, which the planning tests state of [2048, 32768], though one workgroup a row is faster there too)
         // (rows that are written back too are read once here and twice in two passes: kept up to 56
-        // registers -- the gradient of softmax cross-entropy on float32 [1280, 50257] 143.0 -> 108.5 us,
-        // [400, 50257] 50.6 -> 38.0 us, [857, 55520] 92.9 -> 86.6 us; [1220, 65536], 64 registers, 149.4
-        // against 150.4 us)
-        const bool too_long = !resident || (regs > (full_out_ops.empty() ? 48 : 56) && p.fused_depth <= 1) ||
-                              (block == 1024 && regs >= 28 && p.fused_depth <= 1 && full_out_ops.empty());
-        if (too_long || (nr * 2 < device_cu_count() && cols >= 16384) || e.opts.split_rows == 1) {
+        // registers -- the gradient of softmax cross-entropy on float32 [1280, 50257] 143.0 us in two passes, 108.5
+        // here even with one workgroup on a compute unit, [400, 50257] 50.6 and 38.0 us -- and up to 64 in tight rows, two for each compute unit)
+        const int64_t two_a_unit = (int64_t)2 * device_cu_count();
+        const bool adds = std::none_of(red.level_nodes.begin(), red.level_nodes.end(), [&](int n) { return g.nodes[n].op == EWF_RPROD; });
+        const int alone = !full_out_ops.empty() ? 56 : block == 1024 ? 27 : 48;
+        int held = alone;
+        if (!full_out_ops.empty() && park > 0 && nrows >= two_a_unit) held = 64;
+        if (full_out_ops.empty() && tight_possible && words && adds && nrows >= two_a_unit && nrows * cols < ((int64_t)1 << 26)) held = nrows < 2 * two_a_unit ? 44 : 60;
+        const bool too_long = !resident || (regs > held && p.fused_depth <= 1);
+        p.tight_needed = regs > alone && p.fused_depth <= 1;
+        if (too_long || (nrows * 2 < device_cu_count() && cols >= 16384) || e.opts.split_rows == 1) {
             p.row_refused = true;
             return fail(too_long ? "a row does not fit the registers of a workgroup well: the row class would read it once per reduction level or run one workgroup per compute unit"
                                  : "too few rows for one workgroup per row to occupy the chip");
         }
     }
+    if (!tight) park = 0;
+    auto parked = [&](int k) { return park > 0 && parkable(k); };
     const int U = resident ? (int)NV : (e.opts.unroll > 0 ? e.opts.unroll : 4);
     p.tile[in_d] = cols;
     // Maxima and arg-maxima of a float input row that waits in registers are taken the cheap way
@@ -109,6 +148,9 @@ ewf_status Gen::gen_row()
     // row holds a NaN or an infinity, then the index by the threads that hold the maximum.  Only a
     // row whose check word is NaN is folded again with the rules that rank NaN.  (Per element: one
     // and a half instructions instead of five on a dependent chain.)
+    auto has_argmax = [&](const std::vector<int> &nodes) {
+        return std::any_of(nodes.begin(), nodes.end(), [&](int n) { return g.nodes[n].op == EWF_RARGMAX; });
+    };
     std::vector<std::vector<int>> fastn(D + 1);
     std::vector<int> fast_op(D + 1, -1);
     if (resident && !e.opts.plain_extremes) {
@@ -127,14 +169,14 @@ ewf_status Gen::gen_row()
             lvl[l] = rest;
         }
     }
-    {
+    if (tight) {
+        auto_waves_per_simd = p.no_auto_occupancy ? 0 : 8;
+    } else {
         // When all rows can be resident on the chip at once there is no second round of
         // workgroups (whose tail would idle most of the chip): ask the compiler for the
         // register budget that lets that many wavefronts share a SIMD, if the row leaves
         // room for the arithmetic under it.
-        int64_t nrows_ = 1;
-        for (int d = 0; d < R - 1; d++) nrows_ *= c.extent[d];
-        const int64_t wg_per_cu = ceil_div(nrows_, device_cu_count());
+        const int64_t wg_per_cu = ceil_div(nrows, device_cu_count());
         const int64_t waves = ceil_div(wg_per_cu * (block / 64), 4);
         if (resident && !p.no_auto_occupancy && waves >= 2 && waves <= 8 && regs + 40 <= 512 / waves / 8 * 8) {
             auto_waves_per_simd = (int)waves;
@@ -156,15 +198,11 @@ ewf_status Gen::gen_row()
     for (int l = 1; l <= D; l++)
         if (!fastn[l].empty())
             o << "    __shared__ AccS" << l << " sm_accs" << l << "[EWF_NWAVES];\n    __shared__ ewf_fmax sm_fm" << l
-              << "[EWF_NWAVES];\n    __shared__ int sm_ix" << l << "[EWF_NWAVES];\n";
+              << "[EWF_NWAVES];\n" << (has_argmax(fastn[l]) ? "    __shared__ int sm_ix" + std::to_string(l) + "[EWF_NWAVES];\n" : std::string(""));
+    for (int k : row_ops)
+        if (parked(k)) o << "    __shared__ ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> park_" << opname(k) << "[" << park << " * EWF_BLOCK];\n";
     if (has_cross) o << "    AccX *const partials = (AccX *)p.ws_partials;\n";
-    // one workgroup per row when the grid can hold them all: no loop, so nothing is hoisted
-    // out of it into registers that the row needs
-    int64_t nrows = 1;
-    for (int d = 0; d < R - 1; d++) nrows *= c.extent[d];
-    if (nrows >= ((int64_t)1 << 31) - 1) return fail("too many rows");
-    const int64_t grid_cap = e.opts.max_blocks > 0 ? e.opts.max_blocks : (int64_t)256 * 32;
-    if (nrows <= grid_cap) o << "    if ((idx_t)blockIdx.x < p.nrows) {\n        const idx_t row = blockIdx.x;\n";
+    if (!row_loop) o << "    if ((idx_t)blockIdx.x < p.nrows) {\n        const idx_t row = blockIdx.x;\n";
     else o << "    for (idx_t row = blockIdx.x; row < p.nrows; row += gridDim.x) {\n";
     o << "        idx_t t_ = row;\n";
     std::vector<int> outer;
@@ -184,15 +222,12 @@ ewf_status Gen::gen_row()
     for (int k : full_out_ops) base_once(k, "        ");
 
     // the loop over the row: either over register-resident vectors or streaming chunks
-    // The first NFULL steps of a resident row are in range for every thread of the
-    // workgroup at this plan's row length: straight-line code there lets the compiler wait
-    // for the loads one by one instead of for all of them.  (The row length is part of the
-    // plan's key, and NFULL of the generated text, so the assumption travels with the code.)
-    const int64_t NFULL = resident ? cols / per_iter : 0;
+    int pass = 0;
+    std::string me = "tid";                            // the thread's number as the current pass of a tight row knows it
     auto open_pass = [&]() {
         if (resident) {
             o << "        #pragma unroll\n        for (int u = 0; u < " << U << "; ++u) {\n";
-            o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + tid) * EWF_VEC;\n";
+            o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + " << me << ") * EWF_VEC;\n";
             o << "            if (u >= " << NFULL << " && col >= cols) continue;\n";
         } else {
             o << "        for (idx_t c0 = 0; c0 < cols; c0 += " << (per_iter * U) << ") {\n";
@@ -244,6 +279,7 @@ ewf_status Gen::gen_row()
         base_once(k, "        ");
         o << "        const " << ctype(c.ops[k].storage) << " g_" << opname(k) << " = ewf_ld_uniform(q_" << opname(k) << ");\n";
     }
+    const std::string in_lds = "u >= " + std::to_string(NFULL - park) + " && u < " + std::to_string(NFULL);
     if (resident) {
         for (int k : row_ops) if (!late[k]) o << "        ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> x_" << opname(k) << "[" << U << "];\n";
         if (NFULL > 0 || !ragged) {
@@ -254,7 +290,12 @@ ewf_status Gen::gen_row()
                 o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + tid) * EWF_VEC;\n";
             }
             else open_pass();
-            for (int k : row_ops) if (!late[k]) emit_row_load(k, "            ", "x_" + opname(k) + "[u]");
+            for (int k : row_ops) {
+                if (late[k]) continue;
+                if (parked(k)) o << "            if (" << in_lds << ") ewf_ld_lds<" << ctype(c.ops[k].storage) << ", EWF_VEC, " << (c.ops[k].stream ? "true" : "false") << ">(q_" << opname(k) << " + col, park_" << opname(k)
+                                 << " + ((u - " << NFULL - park << ") * EWF_BLOCK + ewf_uniform(tid & ~63)));\n            else\n";
+                emit_row_load(k, "            ", "x_" + opname(k) + "[u]");
+            }
             close_pass();
         }
         if (ragged) {
@@ -279,10 +320,27 @@ ewf_status Gen::gen_row()
         }
     }
 
+    // the vector of step u of a parked operand; the first pass over the row waits for the loads behind the steps in registers
+    bool waited = park == 0;
+    auto take_vec = [&](int k) {
+        const std::string nm = opname(k);
+        if (!waited) o << "            if (u == " << NFULL - park << ") ewf_wait_loads();\n";
+        waited = true;
+        o << "            ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> w_" << nm << ";\n            if (" << in_lds << ") w_" << nm << " = park_" << nm
+          << "[(u - " << NFULL - park << ") * EWF_BLOCK + " << me << "]; else w_" << nm << " = x_" << nm << "[u];\n";
+    };
+    auto forget = [&]() {
+        if (!tight) return;
+        me = "tid" + std::to_string(++pass);
+        o << "        const int " << me << " = ewf_forget(tid) & (EWF_BLOCK - 1);\n";
+        if (pass == 1) return;                         // (nothing computed yet, and the first pass need not wait for every load)
+        for (int k : row_ops)
+            if (!late[k]) o << "        #pragma unroll\n        for (int u = 0; u < " << U << "; ++u) ewf_forget(x_" << opname(k) << "[u]);\n";
+    };
     EmitCtx cx;
     cx.input = [&](int k) {
         if (c.ops[k].stride[in_d] == 0) return "ewf_in(g_" + opname(k) + ")";
-        return resident && !late[k] ? "ewf_in(x_" + opname(k) + "[u].e[e_])" : "ewf_in(w_" + opname(k) + ".e[e_])";
+        return resident && !late[k] && !parked(k) ? "ewf_in(x_" + opname(k) + "[u].e[e_])" : "ewf_in(w_" + opname(k) + ".e[e_])";
     };
     cx.coord = [&](int d) {
         if (d == in_d) return std::string("col + e_");
@@ -290,7 +348,8 @@ ewf_status Gen::gen_row()
     };
     auto stream_loads = [&](const std::vector<char> &need) {
         for (int k : inputs_of(need)) {
-            if (c.ops[k].stride[in_d] == 0 || (resident && !late[k])) continue;
+            if (c.ops[k].stride[in_d] == 0) continue;
+            if (resident && !late[k]) { if (parked(k)) take_vec(k); continue; }
             o << "            ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> w_" << opname(k) << ";\n";
             emit_row_load(k, "            ", "w_" + opname(k));
         }
@@ -321,34 +380,41 @@ ewf_status Gen::gen_row()
             o << "            r" << ga.node << " = in_ ? x_ + 0.0f : 0.0f;\n        }\n";
         }
         if (!fastn[l].empty()) {
-            const std::string L = std::to_string(l), xr = "x_" + opname(fast_op[l]);
-            const char *fold = nrows <= grid_cap ? "ewf_block_reduce_once" : "ewf_block_reduce";
-            o << "        float rr_max" << L << "; int rr_arg" << L << ";\n        {\n";
+            forget();
+            const bool fp = parked(fast_op[l]);
+            const std::string L = std::to_string(l), xr = (fp ? "w_" : "x_") + opname(fast_op[l]) + (fp ? "" : "[u]");
+            const char *fold = row_loop ? "ewf_block_reduce" : "ewf_block_reduce_once";
+            const bool want_index = has_argmax(fastn[l]);
+            o << "        float rr_max" << L << ";" << (want_index ? " int rr_arg" + L + ";" : "") << "\n        {\n";
             o << "        ewf_fmax fm_; fm_.m = ewf_bits_f32(0xff800000u); fm_.c = 0.0f;\n";
             open_pass();
+            if (fp) take_vec(fast_op[l]);
             o << "            { float s_ = 0.0f;\n";
             o << "              _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
             if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
-            o << "                const float t_ = ewf_in(" << xr << "[u].e[e_]);\n";
+            o << "                const float t_ = ewf_in(" << xr << ".e[e_]);\n";
             o << "                fm_.m = __builtin_fmaxf(fm_.m, t_); s_ += t_;\n              }\n";
             o << "              fm_.c = __builtin_fmaf(s_, 0.0f, fm_.c); }\n";
             close_pass();
-            o << "        const float tm_ = fm_.m;\n";
+            if (want_index) o << "        const float tm_ = fm_.m;\n";
             o << "        fm_ = " << fold << "<EWF_NWAVES>(fm_, ewf_fmax_combine(), sm_fm" << L << ", tid);\n";
             o << "        if (fm_.c == fm_.c) {\n";
             // the same bits in every thread (each folds the same per-wavefront values in the same
             // order), so the branch is uniform across the workgroup
-            o << "            int ix_ = 2147483647;\n";
-            o << "            if (tm_ == fm_.m) {\n";
-            o << "                #pragma unroll\n                for (int u = " << U - 1 << "; u >= 0; --u) {\n";
-            o << "                    const idx_t col = (idx_t)(u * EWF_BLOCK + tid) * EWF_VEC;\n";
-            o << "                    if (u >= " << NFULL << " && col >= cols) continue;\n";
-            o << "                    _Pragma(\"unroll\") for (int e_ = EWF_VEC - 1; e_ >= 0; --e_) {\n";
-            if (ragged) o << "                        if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
-            o << "                        if (ewf_in(" << xr << "[u].e[e_]) == fm_.m) ix_ = (int)(col + e_);\n";
-            o << "                    }\n                }\n            }\n";
-            o << "            ix_ = " << fold << "<EWF_NWAVES>(ix_, ewf_imin(), sm_ix" << L << ", tid);\n";
-            o << "            rr_max" << L << " = fm_.m; rr_arg" << L << " = ix_;\n";
+            if (want_index) {
+                o << "            int ix_ = 2147483647;\n";
+                o << "            if (tm_ == fm_.m) {\n";
+                o << "                #pragma unroll\n                for (int u = " << U - 1 << "; u >= 0; --u) {\n";
+                o << "                    const idx_t col = (idx_t)(u * EWF_BLOCK + " << me << ") * EWF_VEC;\n";
+                o << "                    if (u >= " << NFULL << " && col >= cols) continue;\n";
+                if (fp) take_vec(fast_op[l]);
+                o << "                    _Pragma(\"unroll\") for (int e_ = EWF_VEC - 1; e_ >= 0; --e_) {\n";
+                if (ragged) o << "                        if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
+                o << "                        if (ewf_in(" << xr << ".e[e_]) == fm_.m) ix_ = (int)(col + e_);\n";
+                o << "                    }\n                }\n            }\n";
+                o << "            ix_ = " << fold << "<EWF_NWAVES>(ix_, ewf_imin(), sm_ix" << L << ", tid);\n";
+            }
+            o << "            rr_max" << L << " = fm_.m;" << (want_index ? " rr_arg" + L + " = ix_;" : "") << "\n";
             o << "        } else {\n";
             {
                 // a NaN or an infinity somewhere in the row: the fold that ranks them
@@ -358,6 +424,7 @@ ewf_status Gen::gen_row()
                 std::vector<char> need = needed(tg);
                 o << "        " << an << " " << av << " = " << an << "_identity();\n";
                 open_pass();
+                if (fp) take_vec(fast_op[l]);
                 o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
                 if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
                 emit_values(need, cx, "                ");
@@ -379,6 +446,7 @@ ewf_status Gen::gen_row()
                   << (g.nodes[n].op == EWF_RARGMAX ? "arg" : "max") << L << ";\n";
         }
         if (lvl[l].empty()) continue;
+        forget();
         std::string an = "Acc" + std::to_string(l), av = "acc" + std::to_string(l);
         std::vector<int> tg;
         for (int n : lvl[l]) tg.push_back(g.nodes[n].args[0]);
@@ -390,7 +458,8 @@ ewf_status Gen::gen_row()
         // otherwise round more often than those of rows split over workgroups; four chains instead
         // of one change the error by nothing and take 0.5 us of 108).
         const Chains ch = chain_slots(lvl[l]);
-        const bool chains = resident && regs > 48 && ch.any;
+        // (so are they in shorter rows that are not split because they may be tight)
+        const bool chains = resident && (regs > 48 || tight_possible) && ch.any;
         open_pass();
         stream_loads(need);
         if (chains) o << "            " << an << " part_ = " << an << "_identity();\n";
@@ -406,7 +475,7 @@ ewf_status Gen::gen_row()
         // every thread walks its columns in increasing order, starting at tid * EWF_VEC
         emit_first_index(av, lvl[l], "(idx_t)tid * EWF_VEC < cols", "tid * EWF_VEC", "        ");
         // (every level has a buffer of its own: without a loop over rows it is written once)
-        o << "        " << av << " = " << (nrows <= grid_cap ? "ewf_block_reduce_once" : "ewf_block_reduce") << "<EWF_NWAVES>(" << av << ", "
+        o << "        " << av << " = " << (row_loop ? "ewf_block_reduce" : "ewf_block_reduce_once") << "<EWF_NWAVES>(" << av << ", "
           << an << "_combine(), sm_acc" << l << ", tid);\n";
         emit_results(av, lvl[l], "        ");
     }
@@ -415,6 +484,7 @@ ewf_status Gen::gen_row()
         std::vector<int> tg;
         for (int k : full_out_ops) tg.push_back(g.outputs[c.ops[k].index].value);
         std::vector<char> need = needed(tg);
+        forget();
         open_pass();
         stream_loads(need);
         for (int k : full_out_ops) o << "            ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> y_" << opname(k) << ";\n";
@@ -481,7 +551,7 @@ ewf_status Gen::gen_row()
 
     // ---- launch geometry and argument block
     p.grid = std::max<int64_t>(1, std::min(nrows, grid_cap));
-    p.lds_bytes = 0;
+    p.lds_bytes = (int)(park * std::count_if(row_ops.begin(), row_ops.end(), parkable) * block * 16);
     p.workspace_bytes = 0;
     p.finish_grid = 0;
     if (has_cross) {

@@ -226,6 +226,9 @@ struct Plan {
     std::vector<TempFill> temp_fills;
     bool used_auto_occupancy = false;    // the generator asked for a register budget on its own
     bool no_auto_occupancy = false;      // ... and must not (it made the compiler spill)
+    // Row class: the kernel may be generated to share its compute unit with another workgroup (`tight`); the
+    // row is held by one workgroup only because it may be (`tight_needed`); that has failed (`no_tight`).
+    bool tight_possible = false, tight = false, tight_needed = false, no_tight = false;
 };
 
 struct Exec {
@@ -354,6 +357,7 @@ int device_cu_count();
 void set_cache_dir(const char *path);
 void cache_stats(int *mem_hits, int *disk_hits, int *compiles);
 int64_t code_scratch_bytes(const std::vector<char> &code);
+int64_t code_registers(const std::vector<char> &code);
 int peak_concurrent_compiles();
 
 }  // namespace ewf

@@ -236,13 +236,11 @@ ewf_status load_function(const std::vector<char> &code, const std::string &entry
     return EWF_OK;
 }
 
-// Largest per-lane scratch (register spill) size, in bytes, that the metadata of a code object
-// records for any of its kernels.  The metadata is a MessagePack map; the value follows the
-// key ".private_segment_fixed_size" as an unsigned integer.
-int64_t code_scratch_bytes(const std::vector<char> &code)
+// Largest value that the metadata of a code object records for any of its kernels under `key`.  The
+// metadata is a MessagePack map; the value follows the key as an unsigned integer.
+static int64_t code_metadata(const std::vector<char> &code, const char *key)
 {
-    static const char key[] = ".private_segment_fixed_size";
-    const size_t klen = sizeof key - 1;
+    const size_t klen = strlen(key);
     int64_t worst = 0;
     for (size_t i = 0; i + klen + 1 <= code.size(); i++) {
         if (memcmp(code.data() + i, key, klen) != 0) continue;
@@ -257,6 +255,10 @@ int64_t code_scratch_bytes(const std::vector<char> &code)
     }
     return worst;
 }
+
+// Per-lane scratch (register spill) size in bytes, and vector registers of a thread.
+int64_t code_scratch_bytes(const std::vector<char> &code) { return code_metadata(code, ".private_segment_fixed_size"); }
+int64_t code_registers(const std::vector<char> &code) { return code_metadata(code, ".vgpr_count"); }
 
 // Compute units of the current device; the published MI355X figure when no device is
 // present (planning and compiling need none).

@@ -198,6 +198,31 @@ EWF_DEV void ewf_st_u(T *p, const ewf_vec<T, N> &v, ewf_streamed)
     for (int i = 0; i < B / 16; i++) __builtin_nontemporal_store(s[i], d + i);
 }
 
+// One 16-byte vector per lane from p to the wavefront's own 1 KiB of LDS at `to` (the same address in
+// every lane; lane i's vector lands i vectors behind it), past the registers, with the streaming hint or without.  The data
+// is there after ewf_wait_loads(); a wavefront that only reads back what it asked for needs no barrier.
+template <typename T, int N, bool NT>
+EWF_DEV void ewf_ld_lds(const T *p, ewf_vec<T, N> *to)
+{
+    static_assert(N * sizeof(T) == 16, "sixteen bytes a lane");
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)p, (__attribute__((address_space(3))) void *)to, 16, 0, NT ? 2 : 0);
+}
+EWF_DEV void ewf_wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The value stays as it is, but the compiler no longer knows what has been computed from it.
+EWF_DEV int ewf_forget(int v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+template <typename T, int N>
+EWF_DEV void ewf_forget(ewf_vec<T, N> &v)
+{
+    int *w = reinterpret_cast<int *>(&v);
+#pragma unroll
+    for (int i = 0; i < N * (int)sizeof(T) / 4; i++) w[i] = ewf_forget(w[i]);
+}
+
 // ------------------------------------------------------------------ storage <-> value
 
 EWF_DEV float ewf_in(float x) { return x; }
@@ -468,9 +493,18 @@ EWF_DEV T ewf_fold_pairs(F op, const T *smem)
 
 // ... or one after another.  More than eight meet in pairs: on a chain of sixteen, sums of parts of
 // equal size round twice as far (the sum of 50257 magnitudes per row: relative error 6.7e-8, 4.4e-8 in pairs).
+// Sixteen meet in the same pairs on the lanes of a row: one result per lane is read instead of sixteen, whose
+// registers a row of the row class has not to spare (32 of them for a maximum with its check word).
 template <int NWAVES, typename T, typename F>
 EWF_DEV T ewf_fold_waves(F op, const T *smem)
 {
+    if constexpr (NWAVES == 16) {
+        T v = smem[threadIdx.x & 15];
+        v = op(v, ewf_dpp<0xB1>(v));
+        v = op(v, ewf_dpp<0x4E>(v));
+        v = op(v, ewf_dpp<0x141>(v));
+        return op(v, ewf_dpp<0x140>(v));
+    }
     if constexpr (NWAVES > 8) return ewf_fold_pairs<0, NWAVES>(op, smem);
     T r = smem[0];
 #pragma unroll
