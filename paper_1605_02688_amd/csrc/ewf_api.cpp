@@ -228,6 +228,7 @@ static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
     ewf_status st = EWF_OK;
     const Canon &c = plan->canon;
     bool row_only = false;                     // only the row class covers the expression
+    bool planned = false;                      // generated already
     bool cross_only = false;                   // ... and only because of reductions over the rows
     if (!plan->red.has_reduce) {
         plan->kclass = KernelClass::Tile;
@@ -286,7 +287,8 @@ static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
                 if (c.reduced[d]) seen_reduced = true;
                 else if (seen_reduced) kk = d;
             }
-            if (plan->avoid_short_runs && kk >= 0 && kk < c.rank - 1 && c.total >= ((int64_t)1 << 20)) {
+            if (plan->avoid_short_runs && kk >= 0 && kk < c.rank - 1) {
+                const bool split = c.total >= ((int64_t)1 << 20);
                 int64_t inner = 1, outer = 1;
                 for (int d = 0; d < c.rank; d++) if (c.reduced[d]) (d > kk ? inner : outer) *= c.extent[d];
                 bool ops_ok = true;
@@ -300,7 +302,20 @@ static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
                     if (!(plan->red.axes >> a & 1u) || c.dim_of_axis[a] < 0) continue;
                     (c.dim_of_axis[a] < kk ? outer_axes : inner_axes) |= 1u << a;
                 }
-                if (ops_ok && inner < 2048 && outer >= 2 && outer_axes) {
+                int widest = 2;
+                for (const Operand &op : c.ops) if (op.stride[c.rank - 1] != 0) widest = std::max(widest, op.storage == EWF_F16 ? 2 : 4);
+                // planes that are no whole number of vectors: one sweep over rows of whole images (gen_flat says which)
+                if (ops_ok && inner < 2048 && outer >= 2 && inner * widest % 16 != 0) {
+                    plan->kclass = KernelClass::Col;
+                    plan->flat_strips = true;
+                    planned = generate(e, *plan) == EWF_OK;
+                    if (!planned) {
+                        plan->kclass = KernelClass::TileReduce;
+                        plan->flat_strips = false;
+                        plan->layout = ParamLayout();
+                    }
+                }
+                if (!planned && split && ops_ok && inner < 2048 && outer >= 2 && outer_axes) {
                     plan->axes_refused = true;
                     // Which axes the first pass takes.  The outer ones leave a column kernel whose
                     // columns are the kept and the inner dimensions; the inner ones leave short
@@ -343,7 +358,7 @@ static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
             if (st == EWF_EUNSUPPORTED) plan->kclass = KernelClass::Row;      // e.g. too many row operands for one thread
         }
     }
-    if (plan->kclass != KernelClass::Lane) st = generate(e, *plan);
+    if (plan->kclass != KernelClass::Lane && !planned) st = generate(e, *plan);
     if (st == EWF_EUNSUPPORTED && plan->row_refused && plan->kclass == KernelClass::Row && (!row_only || cross_only)) {
         // plain row reductions do not need the row class, nor does a single level of them followed
         // by reductions over the rows (those are folded by the finish kernel)

@@ -181,7 +181,7 @@ ewf_status generate(const Exec &e, Plan &p)
     case KernelClass::Tile: return gen.gen_tile(false);
     case KernelClass::TileReduce: return gen.gen_tile(true);
     case KernelClass::Row: return gen.gen_row();
-    case KernelClass::Col: return gen.gen_col();
+    case KernelClass::Col: return p.flat_strips ? gen.gen_flat() : gen.gen_col();
     case KernelClass::Lane: return gen.gen_lane();
     default: set_error("no kernel class"); return EWF_EUNSUPPORTED;
     }

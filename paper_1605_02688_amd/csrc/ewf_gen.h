@@ -1103,6 +1103,8 @@ struct Gen {
     ewf_status gen_lane();
     ewf_status gen_row();
     ewf_status gen_col();
+    ewf_status gen_flat();
+    void emit_finish_columns(const std::vector<int> &level, const std::vector<int> &group_out_ops, int chains = 4);
 };
 
 

@@ -534,47 +534,7 @@ ewf_status Gen::gen_col()
     if (one_tile) { /* no second kernel */ }
     else if (fin_lanes) emit_finish_lanes(level, group_out_ops, "p.nslots", fin_block,
                                      (int)std::min<int64_t>(8, std::max<int64_t>(1, ceil_div(nslots, fin_block))));
-    else {
-    o << "\nextern \"C\" __global__ void __launch_bounds__(256) ewf_finish(const Params p)\n{\n";
-    o << "    const Acc *const partials = (const Acc *)p.ws_partials;\n";
-    o << "    for (idx_t group = blockIdx.x * 256 + threadIdx.x; group < p.nrows; group += gridDim.x * 256) {\n";
-    // (four chains, met at the end: a quarter of the roundings and of the dependent operations of one)
-    o << "        Acc a_[4];\n";
-    o << "        _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) a_[i_] = Acc_identity();\n";
-    o << "        idx_t s_ = 0;\n";
-    o << "        _Pragma(\"unroll 2\") for (; s_ + 4 <= p.nslots; s_ += 4) {\n";
-    o << "            _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) a_[i_] = Acc_combine()(a_[i_], partials[(size_t)(s_ + i_) * (size_t)p.nrows + (size_t)group]);\n";
-    o << "        }\n";
-    o << "        for (; s_ < p.nslots; ++s_) a_[0] = Acc_combine()(a_[0], partials[(size_t)s_ * (size_t)p.nrows + (size_t)group]);\n";
-    o << "        const Acc tot = Acc_combine()(Acc_combine()(a_[0], a_[1]), Acc_combine()(a_[2], a_[3]));\n";
-    o << "        idx_t g_ = group;\n";
-    for (int d = R - 1; d >= 0; d--) {
-        if (c.reduced[d]) { o << "        const idx_t o" << d << " = 0;\n"; continue; }
-        bool last_kept = true;
-        for (int d2 = d - 1; d2 >= 0; d2--) if (!c.reduced[d2]) last_kept = false;
-        if (!last_kept) o << "        const idx_t o" << d << " = g_ % p.ext[" << d << "]; g_ /= p.ext[" << d << "];\n";
-        else o << "        const idx_t o" << d << " = g_;\n";
-    }
-    for (int d = 0; d < R; d++) o << "        (void)o" << d << ";\n";
-    emit_results("tot", level, "        ");
-    {
-        std::vector<int> gt;
-        for (int k : group_out_ops) gt.push_back(g.outputs[c.ops[k].index].value);
-        std::vector<char> gneed = needed(gt);
-        for (int k : inputs_of(gneed)) emit_base(k, all_dims, "        ");
-        EmitCtx gx;
-        gx.input = [&](int k) { return "ewf_in(q_" + opname(k) + "[0])"; };
-        gx.coord = [&](int d) { return "o" + std::to_string(d); };
-        emit_values(gneed, gx, "        ");
-        for (int k : group_out_ops) {
-            const Operand &op = c.ops[k];
-            const char *cv = op.storage == EWF_F16 ? "ewf_out_f16" : op.storage == EWF_I32 ? "ewf_out_i32" : "ewf_out_f32";
-            emit_base(k, all_dims, "        ");
-            o << "        q_" << opname(k) << "[0] = " << cv << "(v" << g.outputs[op.index].value << ");\n";
-        }
-    }
-    o << "    }\n}\n";
-    }
+    else emit_finish_columns(level, group_out_ops);
 
     // ---- launch geometry and argument block
     // With outer-index lanes a tile is a few KB, too little to pay for a workgroup's start: a
@@ -605,5 +565,51 @@ ewf_status Gen::gen_col()
     return EWF_OK;
 }
 
+// One thread per column folds its slots.
+void Gen::emit_finish_columns(const std::vector<int> &level, const std::vector<int> &group_out_ops, int chains)
+{
+    std::vector<int> all_dims;
+    for (int d = 0; d < R; d++) all_dims.push_back(d);
+    o << "\nextern \"C\" __global__ void __launch_bounds__(256) ewf_finish(const Params p)\n{\n";
+    o << "    const Acc *const partials = (const Acc *)p.ws_partials;\n";
+    o << "    for (idx_t group = blockIdx.x * 256 + threadIdx.x; group < p.nrows; group += gridDim.x * 256) {\n";
+    // (four chains, met at the end: a quarter of the roundings and of the dependent operations of one)
+    o << "        Acc a_[" << chains << "];\n";
+    o << "        _Pragma(\"unroll\") for (int i_ = 0; i_ < " << chains << "; ++i_) a_[i_] = Acc_identity();\n";
+    o << "        idx_t s_ = 0;\n";
+    o << "        _Pragma(\"unroll 2\") for (; s_ + " << chains << " <= p.nslots; s_ += " << chains << ") {\n";
+    o << "            _Pragma(\"unroll\") for (int i_ = 0; i_ < " << chains << "; ++i_) a_[i_] = Acc_combine()(a_[i_], partials[(size_t)(s_ + i_) * (size_t)p.nrows + (size_t)group]);\n";
+    o << "        }\n";
+    o << "        for (; s_ < p.nslots; ++s_) a_[0] = Acc_combine()(a_[0], partials[(size_t)s_ * (size_t)p.nrows + (size_t)group]);\n";
+    if (chains == 8) o << "        _Pragma(\"unroll\") for (int i_ = 0; i_ < 4; ++i_) a_[i_] = Acc_combine()(a_[i_], a_[i_ + 4]);\n";
+    o << "        const Acc tot = Acc_combine()(Acc_combine()(a_[0], a_[1]), Acc_combine()(a_[2], a_[3]));\n";
+    o << "        idx_t g_ = group;\n";
+    for (int d = R - 1; d >= 0; d--) {
+        if (c.reduced[d]) { o << "        const idx_t o" << d << " = 0;\n"; continue; }
+        bool last_kept = true;
+        for (int d2 = d - 1; d2 >= 0; d2--) if (!c.reduced[d2]) last_kept = false;
+        if (!last_kept) o << "        const idx_t o" << d << " = g_ % p.ext[" << d << "]; g_ /= p.ext[" << d << "];\n";
+        else o << "        const idx_t o" << d << " = g_;\n";
+    }
+    for (int d = 0; d < R; d++) o << "        (void)o" << d << ";\n";
+    emit_results("tot", level, "        ");
+    {
+        std::vector<int> gt;
+        for (int k : group_out_ops) gt.push_back(g.outputs[c.ops[k].index].value);
+        std::vector<char> gneed = needed(gt);
+        for (int k : inputs_of(gneed)) emit_base(k, all_dims, "        ");
+        EmitCtx gx;
+        gx.input = [&](int k) { return "ewf_in(q_" + opname(k) + "[0])"; };
+        gx.coord = [&](int d) { return "o" + std::to_string(d); };
+        emit_values(gneed, gx, "        ");
+        for (int k : group_out_ops) {
+            const Operand &op = c.ops[k];
+            const char *cv = op.storage == EWF_F16 ? "ewf_out_f16" : op.storage == EWF_I32 ? "ewf_out_i32" : "ewf_out_f32";
+            emit_base(k, all_dims, "        ");
+            o << "        q_" << opname(k) << "[0] = " << cv << "(v" << g.outputs[op.index].value << ");\n";
+        }
+    }
+    o << "    }\n}\n";
+}
 
 }  // namespace ewf

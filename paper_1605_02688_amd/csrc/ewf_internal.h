@@ -189,6 +189,7 @@ struct Plan {
     // on the much smaller result.
     bool avoid_short_runs = false, axes_refused = false;
     uint32_t split_first_axes = 0;
+    bool flat_strips = false;            // column class over rows of whole images (gen_flat)
     KernelClass kclass = KernelClass::None;
     std::vector<Stage> stages;           // KernelClass::Multi only
     std::vector<Temp> temps;
