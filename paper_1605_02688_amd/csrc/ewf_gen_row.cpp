@@ -69,12 +69,44 @@ ewf_status Gen::gen_row()
         while (want < 1024 && (int64_t)want * VEC * 2 < cols) want *= 2;
         if (want > block) { block = want; p.block = block; }
     }
+    const bool loose = p.loose_vec;
+    // Rows that do not start on cache lines and are written back: the vectors start on the output's lines instead of with the row
+    // (`shifted`), so that a wavefront's 1 KiB is eight whole lines and not parts of nine.  A row's first vector then
+    // begins before it and its last one ends behind it; either is taken as the row's first or last whole vector, of
+    // which the thread counts and writes what is its own.  Gradient of softmax cross-entropy, float32: [1280, 50257] 102.4 ->
+    // 93.5 us (rows of 50304, whole lines, 93.7), [1280, 50260] 101.4 -> 93.1, [1280, 33001] 66.6 -> 61.9, [4000, 7777] 44.3 -> 42.3;
+    // softmax, float32 [4000, 16001] 95.4 -> 88.9, float16 [4000, 16001] 52.8 -> 44.4, [10000, 5003] 40.3 -> 37.7.  Not on short rows,
+    // nor where the memory-side cache holds both tensors (softmax over float16 [20000, 3001] 47.6, shifted 52.3, [300, 16380]
+    // 8.9 and 9.9; the gradient on [4096, 3001] 18.6 and 19.1, on [1280, 10004], aligned to 16 bytes, 20.0 and 20.5).
+    bool shifted = !full_out_ops.empty();
+    if (shifted) {
+        const int64_t row_bytes = cols * isz(c.ops[full_out_ops[0]].storage), rows = c.total / cols;
+        int64_t moved = 0;
+        for (int k : row_ops) moved += isz(c.ops[k].storage);
+        for (int k : full_out_ops) moved += isz(c.ops[k].storage);
+        shifted = row_bytes >= (VEC > 4 ? 10000 : 8000) && rows * cols * moved >= 100000000 && (loose || c.total >= (int64_t)1 << 24);
+        bool off_lines = false;
+        std::vector<int> walked = row_ops;
+        walked.insert(walked.end(), full_out_ops.begin(), full_out_ops.end());
+        for (int k : walked) {
+            const Operand &op = c.ops[k];
+            if (late[k] || op.access != Access::Vector || VEC * isz(op.storage) % 4) shifted = false;
+            for (int d = 0; d < R - 1; d++) off_lines = off_lines || op.stride[d] * isz(op.storage) % 128;
+        }
+        for (int n : red.level_nodes) if (g.nodes[n].op == EWF_RARGMAX) shifted = false;
+        shifted = shifted && off_lines;
+    }
+    // (and then 1024 threads from where others take 512: softmax over [4000, 13001] 71.6 -> 68.6 us, [4000, 16001] 88.9 -> 85.5,
+    // the gradient on [1500, 24003] 56.2 -> 52.5, on [1280, 20001] 37.1 and 37.2; rows of whole vectors, [1280, 24576], 44.8 and 46.1)
+    if (shifted && loose && VEC == 4 && block == 512 && e.opts.block_threads <= 0) { block = 1024; p.block = block; }
     // ---- residency: keep the row in registers when it fits
     const int64_t per_iter = (int64_t)block * VEC;
-    const int64_t NV = ceil_div(cols, per_iter);
+    const int64_t line = shifted ? 128 / isz(c.ops[full_out_ops[0]].storage) : 1;
+    const int64_t NV = ceil_div(cols + line - 1, per_iter);
     int regs = 0;
     for (int k : row_ops) if (!late[k]) regs += (int)NV * VEC * isz(c.ops[k].storage) / 4;
     const bool resident = NV <= 32 && regs <= 96;
+    if (!resident) shifted = false;
     int64_t nrows = 1;
     for (int d = 0; d < R - 1; d++) nrows *= c.extent[d];
     // one workgroup per row when the grid can hold them all: no loop, so nothing is hoisted
@@ -105,7 +137,7 @@ ewf_status Gen::gen_row()
     int64_t park = 0;                                  // steps of the row that wait in LDS
     if (p.tight_possible && regs > 44) {
         const int64_t nops = std::count_if(row_ops.begin(), row_ops.end(), parkable);
-        if (nops > 0) park = std::min({ceil_div(regs - 44, 4 * nops), NFULL, 65536 / (nops * block * 16)});
+        if (nops > 0) park = std::min({ceil_div(regs - 44, 4 * nops), NFULL - (shifted ? 1 : 0), 65536 / (nops * block * 16)});
         if (regs - 4 * nops * park > 48) { p.tight_possible = false; park = 0; }
     }
     const bool tight_possible = p.tight_possible, tight = p.tight && tight_possible;
@@ -220,6 +252,13 @@ ewf_status Gen::gen_row()
     for (int k : row_ops) base_once(k, "        ");
     for (int k : splat_ops) base_once(k, "        ");
     for (int k : full_out_ops) base_once(k, "        ");
+    // (lines as they lie when the tensor starts on one: which elements a thread takes depends on the layout, never on the address)
+    if (shifted) {
+        const int k = full_out_ops[0];
+        std::string at;
+        for (int d : outer) if (c.ops[k].stride[d] != 0) at += (at.empty() ? "" : " + ") + ("o" + std::to_string(d)) + " * p.st_" + opname(k) + "[" + std::to_string(d) + "]";
+        o << "        const idx_t head_ = (idx_t)((" << (at.empty() ? std::string("0") : at) << ") & " << line - 1 << ");\n";
+    }
 
     // the loop over the row: either over register-resident vectors or streaming chunks
     int pass = 0;
@@ -227,8 +266,15 @@ ewf_status Gen::gen_row()
     auto open_pass = [&]() {
         if (resident) {
             o << "        #pragma unroll\n        for (int u = 0; u < " << U << "; ++u) {\n";
-            o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + " << me << ") * EWF_VEC;\n";
-            o << "            if (u >= " << NFULL << " && col >= cols) continue;\n";
+            if (shifted) {
+                o << "            const idx_t own_ = (idx_t)(u * EWF_BLOCK + " << me << ") * EWF_VEC - head_;\n";
+                o << "            if ((u == 0 && own_ + EWF_VEC <= 0) || (u >= " << NFULL << " && own_ >= cols)) continue;\n";
+                if (loose) o << "            const idx_t col = u == 0 && own_ < 0 ? 0 : u >= " << NFULL << " && own_ + EWF_VEC > cols ? cols - EWF_VEC : own_;\n";
+                else o << "            const idx_t col = own_;\n";
+            } else {
+                o << "            const idx_t col = (idx_t)(u * EWF_BLOCK + " << me << ") * EWF_VEC;\n";
+                o << "            if (u >= " << NFULL << " && col >= cols) continue;\n";
+            }
         } else {
             o << "        for (idx_t c0 = 0; c0 < cols; c0 += " << (per_iter * U) << ") {\n";
             o << "        #pragma unroll\n        for (int u = 0; u < " << U << "; ++u) {\n";
@@ -244,10 +290,12 @@ ewf_status Gen::gen_row()
     // element, and when its length is no whole number of vectors the last one is cut (`ragged`)
     // and moved into place (ewf_move_cut).  The steps below NFULL hold whole vectors for every thread,
     // which the unrolled code knows at compile time.
-    const bool loose = p.loose_vec;
-    const bool ragged = loose && cols % VEC != 0;
+    const bool ragged = loose && cols % VEC != 0 && !shifted;
     const std::string whole = "(u < " + std::to_string(NFULL) + " || col + EWF_VEC <= cols)";
     const std::string inside = ragged ? "if (u < " + std::to_string(NFULL) + " || col + e_ < cols) " : std::string("");
+    // elements of a vector that are not the thread's own
+    const std::string skip = shifted && loose ? "if ((u == 0 && col + e_ >= own_ + EWF_VEC) || (u >= " + std::to_string(NFULL) + " && col + e_ < own_)) continue;\n"
+                             : ragged ? "if (u >= " + std::to_string(NFULL) + " && col + e_ >= cols) continue;\n" : std::string("");
     const std::string cut_len = std::to_string(cols % VEC);
     auto streamed = [&](const Operand &op) { return op.stream && VEC * isz(op.storage) % 16 == 0 ? ", ewf_streamed()" : ""; };
     auto emit_row_load = [&](int k, const std::string &ind, const std::string &dst) {
@@ -391,7 +439,7 @@ ewf_status Gen::gen_row()
             if (fp) take_vec(fast_op[l]);
             o << "            { float s_ = 0.0f;\n";
             o << "              _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
-            if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
+            if (!skip.empty()) o << "                " << skip;
             o << "                const float t_ = ewf_in(" << xr << ".e[e_]);\n";
             o << "                fm_.m = __builtin_fmaxf(fm_.m, t_); s_ += t_;\n              }\n";
             o << "              fm_.c = __builtin_fmaf(s_, 0.0f, fm_.c); }\n";
@@ -426,7 +474,7 @@ ewf_status Gen::gen_row()
                 open_pass();
                 if (fp) take_vec(fast_op[l]);
                 o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
-                if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
+                if (!skip.empty()) o << "                " << skip;
                 emit_values(need, cx, "                ");
                 emit_accumulate(av, fastn[l], [&](int node) { return argmax_index(node, cx.coord); }, "                ", true);
                 o << "            }\n";
@@ -464,7 +512,7 @@ ewf_status Gen::gen_row()
         stream_loads(need);
         if (chains) o << "            " << an << " part_ = " << an << "_identity();\n";
         o << "            _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
-        if (ragged) o << "                if (u >= " << NFULL << " && col + e_ >= cols) continue;\n";
+        if (!skip.empty()) o << "                " << skip;
         emit_values(need, cx, "                ");
         auto index = [&](int node) { return argmax_index(node, cx.coord); };
         if (chains) emit_chains_accumulate(ch, av, av, lvl[l], index, "                ");
@@ -499,7 +547,11 @@ ewf_status Gen::gen_row()
         for (int k : full_out_ops) {
             const Operand &op = c.ops[k];
             std::string nm = opname(k);
-            if (op.access == Access::Vector && loose) {
+            if (shifted && loose) {
+                o << "            if (col == own_) ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << streamed(op) << ");\n";
+                o << "            else { _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) if (col + e_ >= own_ && col + e_ < own_ + EWF_VEC) q_" << nm << "[col + e_] = y_" << nm << ".e[e_]; }\n";
+            }
+            else if (op.access == Access::Vector && loose) {
                 if (ragged) {
                     o << "            if " << whole << " ewf_st_u<" << ctype(op.storage) << ", EWF_VEC>(q_" << nm << " + col, y_" << nm << streamed(op) << ");\n";
                     o << "            else ewf_st_cut<" << ctype(op.storage) << ", EWF_VEC, " << cut_len << ">(q_" << nm << " + col, y_" << nm << ");\n";
