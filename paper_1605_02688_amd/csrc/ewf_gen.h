@@ -434,9 +434,11 @@ struct Gen {
     // strictly greater (or the first NaN), and the index comparison falls away.  The
     // identity index (no element taken yet) must then be resolved by emit_first_index.
     // `only` (one flag per position of `nodes`, or null for all) restricts it to some slots.
+    // With `counted` the accumulators of a thread share one count: the caller keeps it and states its
+    // reciprocal as rn_, and stores it in the slots (emit_counts) before they are merged.
     void emit_accumulate(const std::string &acc, const std::vector<int> &nodes,
                          const std::function<std::string(int)> &argmax_index, const std::string &ind,
-                         bool ascending = false, const std::vector<char> *only = nullptr)
+                         bool ascending = false, const std::vector<char> *only = nullptr, bool counted = false)
     {
         for (size_t i = 0; i < nodes.size(); i++) {
             if (shared_slot(nodes, i) >= 0) continue;
@@ -463,9 +465,9 @@ struct Gen {
                 // the single-pass update: the mean moves by its share of the new deviation, and
                 // the product of the deviations before and after the move is the element's part
                 const std::string nn = acc + ".n" + std::to_string(i), b = acc + ".b" + std::to_string(i);
-                o << ind << "{ " << nn << " += 1.0f;\n"
+                o << ind << "{ " << (counted ? std::string() : nn + " += 1.0f;") << "\n"
                   << ind << "  const float d_ = " << v << " - " << a << ";\n"
-                  << ind << "  " << a << " = __builtin_fmaf(d_, __builtin_amdgcn_rcpf(" << nn << "), " << a << ");\n"
+                  << ind << "  " << a << " = __builtin_fmaf(d_, " << (counted ? std::string("rn_") : "__builtin_amdgcn_rcpf(" + nn + ")") << ", " << a << ");\n"
                   << ind << "  " << b << " = __builtin_fmaf(d_, " << v << " - " << a << ", " << b << "); }\n";
                 break;
             }
@@ -489,6 +491,20 @@ struct Gen {
             }
             }
         }
+    }
+
+    bool counts_elements(const std::vector<int> &nodes) const
+    {
+        for (int n : nodes) if (g.nodes[n].op == kRSumSqCentred) return true;
+        return false;
+    }
+
+    // The shared count `count` of a thread's VEC accumulators goes into their slots.
+    void emit_counts(const std::string &acc, const std::vector<int> &nodes, const std::string &count, const std::string &ind)
+    {
+        for (size_t i = 0; i < nodes.size(); i++)
+            if (g.nodes[nodes[i]].op == kRSumSqCentred)
+                o << ind << "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) " << acc << "[e_].n" << i << " = " << count << ";\n";
     }
 
     // Slots whose result is rounded at every step, in whatever order the elements meet: one flag

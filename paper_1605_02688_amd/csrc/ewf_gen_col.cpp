@@ -367,15 +367,19 @@ ewf_status Gen::gen_col()
         for (int k : load_ops) if (!tile_invariant(k)) emit_load(k, "[" + xi + "]", in2 + "    ");
         o << in2 << "}\n";
     };
+    // A thread meets the same rows in all its columns: the count behind a running mean and its reciprocal, a
+    // quarter-rate instruction, are kept once (per column they were 5 of about 12 issue slots an element).
+    const bool counted = counts_elements(level);
     // their arithmetic, accumulation and element-wise stores
     auto emit_arith = [&](const std::string &in2, const std::string &r0, int guard) {
         o << in2 << "#pragma unroll\n" << in2 << "for (int u = 0; u < " << U << "; ++u) {\n";
         o << in2 << "    const int r_ = " << r0 << " + u * EWF_TY;\n";
         emit_guard(in2, guard);
         for (int k : ew_out_ops) o << in2 << "    ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> y_" << opname(k) << ";\n";
+        if (counted) o << in2 << "    n_ += 1.0f;\n" << in2 << "    const float rn_ = __builtin_amdgcn_rcpf(n_);\n";
         o << in2 << "    _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) {\n";
         emit_values(need, cx, in2 + "        ");
-        emit_accumulate("acc[e_]", level, [&](int node) { return argmax_index(node, cx.coord); }, in2 + "        ");
+        emit_accumulate("acc[e_]", level, [&](int node) { return argmax_index(node, cx.coord); }, in2 + "        ", false, nullptr, counted);
         for (int k : ew_out_ops) {
             const Operand &op = c.ops[k];
             const char *cv = op.storage == EWF_F16 ? "ewf_out_f16" : op.storage == EWF_I32 ? "ewf_out_i32" : "ewf_out_f32";
@@ -480,7 +484,7 @@ ewf_status Gen::gen_col()
         o << in2 << "}\n";
         if (NW > 1 && TZ == 1) o << in2 << "__syncthreads();\n";
     };
-    const std::string acc_init = "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_identity();\n";
+    const std::string acc_init = "_Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) acc[e_] = Acc_identity();" + std::string(counted ? " float n_ = 0.0f;\n" : "\n");
     if (UZ == 1) {
         o << ind << "Acc acc[EWF_VEC];\n" << ind << acc_init;
         // whole trips without a branch, then at most one trip that checks its rows (with the
@@ -501,6 +505,7 @@ ewf_status Gen::gen_col()
             o << ind << "    }\n";
         }
         o << ind << "}\n";
+        if (counted) emit_counts("acc", level, "n_", ind);
         emit_fold_and_write(ind);
     }
     else {
@@ -523,6 +528,7 @@ ewf_status Gen::gen_col()
         o << ind << "#pragma unroll\n" << ind << "for (int z_ = 0; z_ < " << UZ << "; ++z_) {\n" << ind << zhead;
         o << ind << "    Acc acc[EWF_VEC];\n" << ind << "    " << acc_init;
         emit_arith(ind + "    ", "ty", 2);
+        if (counted) emit_counts("acc", level, "n_", ind + "    ");
         emit_fold_and_write(ind + "    ");
         o << ind << "}\n";
     }
