@@ -176,6 +176,21 @@ ewf_status generate(const Exec &e, Plan &p)
         if (wide.gen_lane() == EWF_OK) return EWF_OK;
         p.loose_vec = false;
     }
+    // Sums down columns whose number or alignment allows narrow accesses only: wide vectors at any alignment
+    // (gen_col says which calls qualify).
+    if (p.kclass == KernelClass::Col && !p.flat_strips && c.vec_loose > c.vec && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
+        Gen narrow(e, p);
+        const ewf_status st = narrow.gen_col();
+        if (st != EWF_OK) return st;
+        p.layout = ParamLayout();
+        p.loose_vec = true;
+        Gen wide(e, p);
+        wide.VEC = c.vec_loose;
+        wide.strict_one_launch = p.finish_grid == 0;
+        if (wide.gen_col() == EWF_OK) return EWF_OK;
+        p.loose_vec = false;
+        p.layout = ParamLayout();
+    }
     Gen gen(e, p);
     switch (p.kclass) {
     case KernelClass::Tile: return gen.gen_tile(false);

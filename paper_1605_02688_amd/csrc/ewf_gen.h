@@ -827,6 +827,8 @@ struct Gen {
     // (0: the ordinary budget), in the end without staging.
     int64_t stage_cap = 0;
     bool lds_refused = false;
+    // Column class with vectors of any alignment: the same call in strict vectors takes one launch.
+    bool strict_one_launch = false;
 
     std::string occupancy_attr() const
     {

@@ -33,9 +33,21 @@ ewf_status Gen::gen_col()
         (group ? group_out_ops : ew_out_ops).push_back((int)k);
     }
     const std::vector<int> &level = red.level_nodes;
+    // Vectors that assume element alignment only (see Plan::loose_vec).  The vector that the last column cuts
+    // is read as the last whole one of the row; its columns are then summed by two threads, in the same order,
+    // and both write the same results.  That needs a kernel that writes nothing per element and no result over
+    // a value that the other thread may still read.
+    const bool loose = p.loose_vec;
+    if (loose) {
+        if (!ew_out_ops.empty()) return fail("cut vectors are for columns that are only read");
+        for (const Operand &op : c.ops) {
+            if (op.is_output && op.alias_of >= 0) return fail("cut vectors: a result in the place of an operand");
+            if (!op.is_output && op.stride[in_d] != 0 && op.stride[in_d] != 1) return fail("cut vectors: an operand without unit stride");
+        }
+    }
 
     // ---- thread layout: TX lanes along the columns, TY groups of lanes along the rows
-    const int64_t colvecs = c.extent[in_d] / VEC;
+    const int64_t colvecs = ceil_div(c.extent[in_d], VEC);
     int TX = 64;
     if (colvecs < 64) { TX = 1; while (TX < colvecs) TX *= 2; }
     const bool small = c.total / VEC < (int64_t)256 * 512;
@@ -231,6 +243,7 @@ ewf_status Gen::gen_col()
         T[dR] = std::min(c.extent[dR], tr);
     }
     const int64_t TR = T[dR];
+    const bool cut = loose && c.extent[in_d] % VEC != 0;
     int64_t ntile[kMaxDims], ntiles = 1;
     for (int d = 0; d < R; d++) { ntile[d] = ceil_div(c.extent[d], T[d]); ntiles *= ntile[d]; p.tile[d] = T[d]; }
     if (ntiles >= ((int64_t)1 << 31) - 1 || TR >= ((int64_t)1 << 30)) return fail("tile count out of range");
@@ -240,6 +253,19 @@ ewf_status Gen::gen_col()
         return fail("too many reduction groups");
 
     const bool one_tile = nslots == 1;
+    // Wide vectors at any alignment pay where strips of at least 32 lanes have most of their lanes at work and
+    // there are four workgroups a compute unit, or whole columns as before.  us in strict vectors and here, sums
+    // over axis 0: float16 [4096, 24381] 63.6 and 37.7, float32 90.1 and 66.4; over axis 1 of [64, 1000, 999] 40.4 and
+    // 24.1, 57.3 and 43.2; float16 [500, 129, 189] 9.2 and 6.7; mean and variance of float32 [129760, 411] 53.7 and 46.8.
+    // But (lanes) mean and variance of float16 [100000, 67] 7.4 and 11.7; (workgroups) of [5000, 1001] 5.5 and 11.9,
+    // float32 6.6 and 7.7; (a second launch) sums over axis 1 of float32 [500, 129, 189] 13.4 and 16.4; (strips of
+    // 8 lanes) over axis 0 of float16 [500, 24381] 10.1 and 10.8, (96 workgroups) of [100, 24381] 3.5 and 3.9.
+    if (loose) {
+        const int64_t strips = ceil_div(c.extent[in_d], (int64_t)TX * VEC);
+        if (TX < 32 || TZ > 1 || c.extent[in_d] * 10 < strips * TX * VEC * 7) return fail("cut vectors leave lanes idle");
+        if (one_tile && ntiles * 2 < device_cu_count()) return fail("cut vectors leave too few workgroups");
+        if (!one_tile && (strict_one_launch || ntiles < (int64_t)4 * device_cu_count())) return fail("cut vectors leave too few workgroups");
+    }
     const int NW = block / 64;
     // The second kernel folds a column's partial results either with the lanes of a workgroup
     // (many slots) or in one thread per column (few slots, or a moderate number under so many
@@ -293,13 +319,18 @@ ewf_status Gen::gen_col()
     for (int d = R - 1; d >= 0; d--) {
         if (d > 0) o << "        const idx_t ti" << d << " = ewf_uniform(t_ % p.ntile[" << d << "]); t_ /= p.ntile[" << d << "];\n";
         else o << "        const idx_t ti0 = ewf_uniform(t_);\n";
-        o << "        const idx_t o" << d << " = ti" << d << " * " << T[d] << ";\n";
+        o << "        const idx_t o" << d << " = ";
+        if (d == in_d && cut) o << "ti" << d << " * " << T[d] << " < p.ext[" << d << "] - EWF_VEC ? ti" << d << " * " << T[d] << " : p.ext[" << d << "] - EWF_VEC;\n";
+        else o << "ti" << d << " * " << T[d] << ";\n";
     }
     std::string ind = "        ";
     for (int k : load_ops) emit_base(k, all_dims, ind);
     for (int k : ew_out_ops) emit_base(k, all_dims, ind);
-    o << ind << "const int cc_ = tx * EWF_VEC;\n";
-    o << ind << "const bool colok_ = cc_ < " << TK << " && o" << in_d << " + cc_ < p.ext[" << in_d << "]"
+    const std::string lane_at = cut ? "at_" : "cc_";
+    o << ind << "const int " << lane_at << " = tx * EWF_VEC;\n";
+    if (cut) o << ind << "const int last_ = (int)((p.ext[" << in_d << "] - o" << in_d << ") < " << TK << " ? (p.ext[" << in_d << "] - o" << in_d << ") : " << TK << ") - EWF_VEC;\n"
+               << ind << "const int cc_ = at_ < last_ ? at_ : last_;\n";
+    o << ind << "const bool colok_ = " << lane_at << " < " << TK << " && o" << in_d << " + " << lane_at << " < p.ext[" << in_d << "]"
       << (TZ > 1 && UZ == 1 ? " && o" + std::to_string(dK) + " + tz < p.ext[" + std::to_string(dK) + "]" : std::string("")) << ";\n";
     o << ind << "const int rows_ = (int)((p.ext[" << dR << "] - o" << dR << ") < " << TR << " ? (p.ext[" << dR << "] - o" << dR << ") : " << TR << ");\n";
     // An operand that is the same for every row of the tile (a per-column bias) is loaded once
@@ -322,7 +353,8 @@ ewf_status Gen::gen_col()
         if (op.stride[in_d] == 0)
             o << in2 << "x_" << nm << at << " = *ewf_at(q_" << nm << ", " << off_expr(k) << ");\n";
         else if (op.access == Access::Vector)
-            o << in2 << "x_" << nm << at << " = " << (op.stream ? "ewf_ld_nt<" : "ewf_ld<") << ctype(op.storage) << ", EWF_VEC>(ewf_at(q_" << nm << ", " << off_expr(k) << "));\n";
+            o << in2 << "x_" << nm << at << " = " << (loose ? "ewf_ld_u<" : op.stream ? "ewf_ld_nt<" : "ewf_ld<") << ctype(op.storage) << ", EWF_VEC>(ewf_at(q_" << nm << ", " << off_expr(k) << ")"
+              << (loose && op.stream && VEC * isz(op.storage) % 16 == 0 ? ", ewf_streamed()" : "") << ");\n";
         else {
             o << in2 << "{ const ioff_t b_ = " << off_expr(k) << ";\n";
             o << in2 << "  _Pragma(\"unroll\") for (int e_ = 0; e_ < EWF_VEC; ++e_) x_" << nm << at << ".e[e_] = *ewf_at(q_" << nm
@@ -452,7 +484,7 @@ ewf_status Gen::gen_col()
             o << in2 << "    (void)slot; (void)group;\n";
             std::vector<std::string> coords(R);
             for (int d = 0; d < R; d++) coords[d] = "gc" + std::to_string(d) + "_";
-            auto vector_out = [&](int k) { return VEC > 1 && c.ops[k].access == Access::Vector && c.ops[k].stride[in_d] == 1; };
+            auto vector_out = [&](int k) { return VEC > 1 && !loose && c.ops[k].access == Access::Vector && c.ops[k].stride[in_d] == 1; };
             for (int k : group_out_ops)
                 if (vector_out(k))
                     o << in2 << "    ewf_vec<" << ctype(c.ops[k].storage) << ", EWF_VEC> yg_" << opname(k) << "; "
