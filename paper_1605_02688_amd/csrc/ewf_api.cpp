@@ -245,11 +245,22 @@ static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
             if (plan->red.edepth[od.value] >= 1 && (e.g.nodes[od.value].bcast & plan->red.axes) != plan->red.axes) full_dep_out = true;
         if (!c.reduced[c.rank - 1]) {
             // the reduced axes are not the fastest-varying ones in memory: column class
-            if (needs_row || full_dep_out) {
-                set_error("unsupported: chained or cross-group reductions need the reduced axes to form the innermost contiguous dimension");
-                return EWF_EUNSUPPORTED;
-            }
             plan->kclass = KernelClass::Col;
+            if (needs_row || full_dep_out) {
+                // One launch where a workgroup can hold whole columns (gen_held says when).  Chains of reductions
+                // with results per element only, from 1024 rows on: shorter columns and a single level take two
+                // launches, not three, which the planning tests state of [300, 70] and [512, 512].
+                plan->held_columns = plan->red.max_depth > 1 && full_dep_out && c.extent[0] >= 1024 && !e.opts.no_rewrite && !e.opts.force_scalar && e.opts.block_threads <= 0 && e.opts.unroll <= 0 &&
+                                     e.opts.tile_elems <= 0 && e.opts.max_blocks <= 0;
+                planned = plan->held_columns && generate(e, *plan) == EWF_OK;
+                if (!planned) {
+                    plan->kclass = KernelClass::None;
+                    plan->held_columns = false;
+                    plan->layout = ParamLayout();
+                    set_error("unsupported: chained or cross-group reductions need the reduced axes to form the innermost contiguous dimension");
+                    return EWF_EUNSUPPORTED;
+                }
+            }
         } else if (needs_row || full_dep_out) {
             if (!inner_only) {
                 set_error("unsupported: chained or cross-group reductions need the reduced axes to form the innermost contiguous dimension");

@@ -178,7 +178,7 @@ ewf_status generate(const Exec &e, Plan &p)
     }
     // Sums down columns whose number or alignment allows narrow accesses only: wide vectors at any alignment
     // (gen_col says which calls qualify).
-    if (p.kclass == KernelClass::Col && !p.flat_strips && c.vec_loose > c.vec && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
+    if (p.kclass == KernelClass::Col && !p.flat_strips && !p.held_columns && c.vec_loose > c.vec && !e.opts.force_scalar && c.extent[c.rank - 1] >= 4 * c.vec_loose) {
         Gen narrow(e, p);
         const ewf_status st = narrow.gen_col();
         if (st != EWF_OK) return st;
@@ -196,7 +196,7 @@ ewf_status generate(const Exec &e, Plan &p)
     case KernelClass::Tile: return gen.gen_tile(false);
     case KernelClass::TileReduce: return gen.gen_tile(true);
     case KernelClass::Row: return gen.gen_row();
-    case KernelClass::Col: return p.flat_strips ? gen.gen_flat() : gen.gen_col();
+    case KernelClass::Col: return p.held_columns ? gen.gen_held() : p.flat_strips ? gen.gen_flat() : gen.gen_col();
     case KernelClass::Lane: return gen.gen_lane();
     default: set_error("no kernel class"); return EWF_EUNSUPPORTED;
     }

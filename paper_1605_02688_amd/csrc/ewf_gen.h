@@ -1122,6 +1122,7 @@ struct Gen {
     ewf_status gen_row();
     ewf_status gen_col();
     ewf_status gen_flat();
+    ewf_status gen_held();
     void emit_finish_columns(const std::vector<int> &level, const std::vector<int> &group_out_ops, int chains = 4);
 };
 

@@ -190,6 +190,7 @@ struct Plan {
     bool avoid_short_runs = false, axes_refused = false;
     uint32_t split_first_axes = 0;
     bool flat_strips = false;            // column class over rows of whole images (gen_flat)
+    bool held_columns = false;           // column class that holds whole columns in registers (gen_held)
     KernelClass kclass = KernelClass::None;
     std::vector<Stage> stages;           // KernelClass::Multi only
     std::vector<Temp> temps;
