@@ -43,7 +43,8 @@ std::string layout_signature(const Graph &g, const ewf_tensor *in, int nin, cons
         int orank = g.ndim - __builtin_popcount(v.dropped);
         for (int d = 0; d < orank; d++) { put(out[k].shape[d]); put(out[k].strides[d]); }
         put((int64_t)((uintptr_t)out[k].ptr & 15));
-        // exact aliasing of an input changes nothing in the kernel but must be re-validated
+        // which input an output lies over: kernels in which two threads own an element are not for such
+        // calls (Operand::alias_of)
         int alias = -1;
         for (int j = 0; j < nin; j++) if (in[j].ptr == out[k].ptr) alias = j;
         put(alias);

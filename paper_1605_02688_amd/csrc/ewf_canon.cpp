@@ -205,6 +205,9 @@ ewf_status canonicalize(const Exec &e, const ReduceInfo &red, const ewf_tensor *
     if (check_ptrs) {
         st = check_aliasing(raw, nin, nout);
         if (st != EWF_OK) return st;
+        for (int o = nin; o < nin + nout; o++)
+            for (int k = nin - 1; k >= 0; k--)
+                if (same_view(raw[k], raw[o])) c.ops[o].alias_of = k;
     }
     if (raw_out) *raw_out = raw;
 

@@ -85,11 +85,11 @@ ewf_status Gen::gen_held()
     const int64_t W = std::min<int64_t>((int64_t)TX * VEC, cols), TY = block / TX, NV = ceil_div(rows, TY), NFULL = rows / TY;
     const int64_t strips = ceil_div(cols, W);
     const bool cut = cols % VEC != 0;
-    for (size_t k = nin; k < c.ops.size(); k++) {
-        const bool group = std::find(group_out_ops.begin(), group_out_ops.end(), (int)k) != group_out_ops.end();
-        // (a value that other threads may still read must stay)
-        if (c.ops[k].alias_of >= 0 && (group || cut)) return fail("held columns: a result in the place of an operand");
-    }
+    // (Two threads, in two workgroups where the last strip is one column wide, own the columns that a cut vector shares: a
+    // value that one of them may still read must stay.  Whole vectors are each workgroup's own, and its threads have read
+    // what a column has one of before the first barrier.)
+    for (size_t k = nin; cut && k < c.ops.size(); k++)
+        if (c.ops[k].alias_of >= 0) return fail("held columns: a result in the place of an operand");
     p.block = block;
     p.tile[0] = rows;
     p.tile[1] = W;
