@@ -689,6 +689,15 @@ struct Gen {
         return -1;
     }
 
+    // True if an output that varies along the reduced axes is written over input k: the element that such a sum
+    // reads may then be gone where nothing keeps its read ahead of the other threads' stores.
+    bool written_over(int k) const
+    {
+        for (const Operand &op : c.ops)
+            if (op.is_output && op.alias_of == k && (g.nodes[g.outputs[op.index].value].bcast & red.axes) != red.axes) return true;
+        return false;
+    }
+
     bool match_gather(int n, Gather &out) const
     {
         const Node &nd = g.nodes[n];

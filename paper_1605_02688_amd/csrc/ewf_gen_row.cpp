@@ -39,6 +39,18 @@ ewf_status Gen::gen_row()
         if (match_gather(n, ga) && ga.cdim == in_d) gat[red.edepth[n]].push_back(ga);
         else lvl[red.edepth[n]].push_back(n);
     }
+    // (where no workgroup-wide fold follows, a row that is written over is summed as described: nothing else keeps
+    // the threads that store behind those that read the one element)
+    bool fold_follows = false;
+    for (int l = D; l >= 1; l--) {
+        fold_follows = fold_follows || !lvl[l].empty();
+        for (size_t i = 0; i < gat[l].size() && !fold_follows; i++) {
+            if (!written_over(gat[l][i].input)) continue;
+            lvl[l].push_back(gat[l][i].node);
+            gat[l].erase(gat[l].begin() + i);
+            fold_follows = true;
+        }
+    }
 
     // which inputs vary along the row and are read by some per-element computation
     std::vector<int> elem_targets;

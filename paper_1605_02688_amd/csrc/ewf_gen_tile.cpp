@@ -424,13 +424,13 @@ ewf_status Gen::gen_tile(bool with_reduce)
     std::vector<int> targets;
     for (int k : ew_out_ops) targets.push_back(g.outputs[c.ops[k].index].value);
     // Sums with one non-zero term are left to the second kernel, which reads that element
-    // itself (as long as something else remains to be accumulated here).
+    // itself (as long as something else remains to be accumulated here, and the element stays).
     std::vector<int> level;
     std::vector<Gather> gathers;
     if (with_reduce) {
         for (int n : red.level_nodes) {
             Gather ga;
-            if (match_gather(n, ga) && g.nodes[n].axes == red.axes && c.reduced[ga.cdim]) gathers.push_back(ga);
+            if (match_gather(n, ga) && g.nodes[n].axes == red.axes && c.reduced[ga.cdim] && !written_over(ga.input)) gathers.push_back(ga);
             else level.push_back(n);
         }
         if (level.empty()) { level = red.level_nodes; gathers.clear(); }

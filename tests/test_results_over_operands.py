@@ -1,6 +1,6 @@
 """Results written over an operand (the same pointer, shape and strides): which kernels such calls may take, on the CPU,
-and their parity on the GPU.  Vectors cut by the last column belong to two threads, which may not be where one of them
-still reads what the other has written."""
+and their parity on the GPU.  Vectors cut by the last column belong to two threads, and an operand that does not vary along
+every axis is read by many: neither may be where one of them still reads what another has written."""
 import numpy as np
 import pytest
 
@@ -31,13 +31,21 @@ def _normalised(rows, storage, running):
     return s
 
 
-def _plan(spec, shapes, over):
+def _plan(spec, shapes, over, **opts):
     """Plans for dense tensors; `over` maps an output to the input it is written over."""
-    expr = ewf.Expression(spec)
+    expr = ewf.Expression(spec, **opts)
     ins = [ref(BASE + (k << 32), shape) for k, shape in enumerate(shapes)]
-    outs = [ins[over[k]] if k in over else ref(BASE + (16 + k << 32), shape) for k, shape in enumerate(expr.output_shapes(ins))]
-    expr.plan(ins, outs)
+    outs = [ref(BASE + ((over[k] if k in over else 16 + k) << 32), shape) for k, shape in enumerate(expr.output_shapes(ins))]
+    expr.workspace = expr.plan(ins, outs)
     return expr
+
+
+def _kernels(expr):
+    """The kernel classes of a plan's launches, and the source of each."""
+    info = expr.info()
+    if info["kernel_class"] != "multi": return [info["kernel_class"]], [expr.source()]
+    stages = range(info["grid_blocks"])
+    return [ewf.debug_plan_info(expr.handle, k)["kernel_class"] for k in stages], [ewf.debug_source(expr.handle, k) for k in stages]
 
 
 def _run(G, spec, host, over):
@@ -45,7 +53,7 @@ def _run(G, spec, host, over):
     dev = [torch.from_numpy(a.copy()).cuda() for a in host]
     expr = G.ewf.Expression(spec)
     outs = G.h.alloc_outputs(expr, spec, dev)
-    for k, j in over.items(): outs[k] = dev[j]
+    for k, j in over.items(): outs[k] = dev[j].view(outs[k].shape)
     ws = G.h.make_workspace(expr, dev, outs)
     expr.run(dev, outs, (), ws, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
@@ -84,6 +92,32 @@ def test_held_columns_over_an_operand_keep_to_their_columns(rows, cols, storage,
         assert held(_plan(spec, shapes, over)) == (cols % 2 == 0), over
 
 
+def _picked(rows, cols, total):
+    """One element of a row, chosen by an index, beside a result of the row's length."""
+    s = GraphSpec(2)
+    x, t = s.input("f32", (False, False)), s.input("i32", (False, True))
+    one = s.reduce("sum", s.apply("where", s.apply("eq", s.iota(1), t), x, s.const(0.0)), (1,), keep=True)
+    if total:
+        s.output(s.apply("max", x, s.const(0.0)), "f32")
+        s.output(s.add(one, s.reduce("max", x, (1,), keep=True)), "f32")
+    else:
+        s.output(s.sub(x, one), "f32")
+    return s, [(rows, cols), (rows, 1)]
+
+
+PICKED = [(40, 30000, True), (600, 3000, True), (600, 3000, False), (300, 20011, False), (5000, 500, False)]
+
+
+@pytest.mark.parametrize("rows,cols,total", PICKED)
+def test_an_element_is_not_picked_from_a_row_that_is_gone(rows, cols, total):
+    spec, shapes = _picked(rows, cols, total)
+    picks = lambda expr: [src for src in _kernels(expr)[1] if "const bool in_ = " in src]
+    apart, over = _plan(spec, shapes, {}), _plan(spec, shapes, {0: 0})
+    assert picks(apart)
+    # (a wavefront's loads come before its stores, and a workgroup's before a fold that the stores wait for)
+    assert not picks(over) or over.info()["kernel_class"] == "lane" or (total and over.info()["kernel_class"] == "row")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape,axis,storage", SUMS)
 def test_sums_over_an_operand(shape, axis, storage, oracle, G):
@@ -105,3 +139,23 @@ def test_normalisation_over_its_input(rows, cols, storage, oracle, G):
     print(f"[case] {storage} {rows} {cols}", flush=True)
     _, got = _run(G, spec, [x], {0: 0})
     G.h.compare("normalised", got[0], oracle.evaluate(spec, [x], nthreads=4)[0], *(G.h.ELEMENTWISE if storage == "f32" else G.h.HALF))
+
+
+def _inputs(spec, shapes, rng):
+    out = []
+    kinds = [n[2] for n in spec.nodes if n[0] == "input"]
+    for storage, shape in zip(kinds, shapes):
+        if storage == "i32": out.append(rng.integers(0, shapes[0][1], shape).astype(np.int32))
+        else: out.append(rng.uniform(0.5, 1.5, shape).astype(np.float32))
+    return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,cols,total", PICKED)
+def test_picked_elements_over_their_row(rows, cols, total, oracle, G):
+    spec, shapes = _picked(rows, cols, total)
+    host = _inputs(spec, shapes, np.random.default_rng(rows))
+    host[0] -= np.float32(1.0)
+    print(f"[case] {rows} {cols} {total}", flush=True)
+    _, got = _run(G, spec, host, {0: 0})
+    for k, w in enumerate(oracle.evaluate(spec, host, nthreads=4)): G.h.compare(f"output {k}", got[k], w, *G.h.ELEMENTWISE)
