@@ -224,10 +224,42 @@ ewf_status make_plan(Exec &e, const ewf_tensor *in, int nin, const ewf_tensor *o
     return EWF_OK;
 }
 
+// An output that lies over an operand of which several threads read the same element is safe in one kernel only
+// where it is written behind all of them: a value per group of the reduced axes, by the group's own workgroup or
+// the second kernel, and what a reduction over the groups gives, by the last thread.  Anything else (the same
+// value written by every row, next to rows that still read what it lies over) takes a pass of its own.
+static bool overwrites_shared_operand(const Exec &e, const Plan &p, const int64_t *full)
+{
+    const Graph &g = e.g;
+    uint32_t varied = 0;
+    for (int d = 0; d < g.ndim; d++) if (full[d] > 1) varied |= 1u << d;
+    std::vector<char> after_cross(g.nodes.size(), 0);
+    for (int n : p.red.cross_nodes) after_cross[n] = 1;
+    for (size_t n = 0; n < g.nodes.size(); n++)
+        for (int a = 0; a < g.nodes[n].nargs; a++) if (after_cross[g.nodes[n].args[a]]) after_cross[n] = 1;
+    std::vector<char> live(g.nodes.size(), 0);
+    for (const OutputDecl &o : g.outputs) live[o.value] = 1;
+    for (int n = (int)g.nodes.size() - 1; n >= 0; n--)
+        if (live[n]) for (int a = 0; a < g.nodes[n].nargs; a++) live[g.nodes[n].args[a]] = 1;
+    for (size_t k = 0; k < g.outputs.size(); k++) {
+        const int v = g.outputs[k].value;
+        const uint32_t same = g.nodes[v].bcast & varied;
+        if (p.canon.ops[g.ninputs + k].alias_of < 0 || !same || after_cross[v]) continue;
+        if (p.red.has_reduce && same == (p.red.axes & varied)) continue;
+        for (int i = 0; i < g.ninputs; i++)
+            if (live[g.input_node[i]] && p.canon.ops[i].addr == p.canon.ops[g.ninputs + k].addr) return true;
+    }
+    return false;
+}
+
 static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
 {
     ewf_status st = EWF_OK;
     const Canon &c = plan->canon;
+    if (overwrites_shared_operand(e, *plan, full)) {
+        set_error("unsupported: a result lies over an operand that other threads of the same kernel read");
+        return EWF_EUNSUPPORTED;
+    }
     bool row_only = false;                     // only the row class covers the expression
     bool planned = false;                      // generated already
     bool cross_only = false;                   // ... and only because of reductions over the rows

@@ -10,6 +10,7 @@
 // kernel.  Every stage is an ordinary sub-expression with its own executable and plan cache.
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <map>
 
 #include "ewf_internal.h"
@@ -81,6 +82,160 @@ void build_stage(const Graph &g, const std::vector<std::pair<int, ewf_dtype>> &t
     for (auto &t : targets) h.outputs.push_back({pos[t.first], t.second});
 }
 
+size_t align_up(size_t v) { return (v + 255) / 256 * 256; }
+
+// A temporary in the workspace for the values of node n.
+Temp temp_for(const Graph &g, int n, const int64_t *full, size_t &ws)
+{
+    Temp t;
+    t.dtype = g.nodes[n].vtype == EWF_I32 ? EWF_I32 : EWF_F32;
+    int64_t count = 1;
+    for (int d = g.ndim - 1; d >= 0; d--) {
+        t.shape[d] = (g.nodes[n].bcast & (1u << d)) ? 1 : full[d];
+        t.strides[d] = count;
+        count *= t.shape[d];
+    }
+    t.bytes = (size_t)count * 4;
+    t.offset = ws;
+    ws = align_up(ws + t.bytes);
+    return t;
+}
+
+// The input that output k lies over where several threads may read the same element of it (it does not
+// vary along every axis), or -1.  A kernel must not write such a result while others still read the
+// operand: single_kernel_plan says which kernels do not.
+std::vector<int> shared_operands(const Graph &g, uint32_t unit, const ewf_tensor *in, int nin, const ewf_tensor *out, int nout)
+{
+    std::vector<int> over(nout, -1);
+    for (int k = 0; k < nout; k++) {
+        if (!(g.nodes[g.outputs[k].value].bcast & ~unit) || !out[k].ptr) continue;
+        for (int i = 0; i < nin; i++) if (in[i].ptr == out[k].ptr) over[k] = i;
+    }
+    return over;
+}
+
+// What `value` is computed from, up to the materialised nodes and those flagged in `stop`.
+std::vector<char> cone_of(const Graph &g, int value, const std::map<int, int> &cuts, const std::vector<char> *stop = nullptr)
+{
+    std::vector<char> cone(g.nodes.size(), 0);
+    cone[value] = 1;
+    for (int n = value; n >= 0; n--) {
+        if (!cone[n] || cuts.count(n) || (stop && (*stop)[n])) { cone[n] = 0; continue; }
+        for (int a = 0; a < g.nodes[n].nargs; a++) cone[g.nodes[n].args[a]] = 1;
+    }
+    return cone;
+}
+
+// True if a node of `cone` is an input at address `ptr`.
+bool reads_from(const Graph &g, const std::vector<char> &cone, const ewf_tensor *in, const void *ptr)
+{
+    for (size_t n = 0; n < cone.size(); n++)
+        if (cone[n] && g.nodes[n].kind == NodeKind::Input && in[g.nodes[n].index].ptr == ptr) return true;
+    return false;
+}
+
+typedef std::function<ewf_status(Stage &)> TryStage;
+
+// The last stages of a plan one of whose results lies over a shared operand: the other outputs of `outs` in
+// one stage, then each such result in a stage of its own, whose space is the result's.  A result that reads
+// what another output lies over is computed into a temporary before either is written, and copied at the end.
+// EWF_EUNSUPPORTED, with nothing added to the plan, while a reduction is left or the other outputs do not
+// fit one kernel.
+ewf_status plan_shared_results(const Graph &g, const std::vector<int> &outs, const std::vector<int> &over, const std::map<int, int> &cuts,
+                               const int64_t *full, uint32_t unit, const ewf_tensor *in, const ewf_tensor *out, int nout,
+                               Plan &plan, size_t &ws, const TryStage &try_stage)
+{
+    const size_t nstages = plan.stages.size(), ntemps = plan.temps.size(), ws0 = ws;
+    auto refused = [&](ewf_status st) {
+        plan.stages.resize(nstages);
+        plan.temps.resize(ntemps);
+        ws = ws0;
+        return st;
+    };
+    std::vector<int> last;
+    std::vector<std::pair<int, ewf_dtype>> targets;
+    Stage rest;
+    for (int k : outs) {
+        if (over[k] < 0) { targets.push_back({g.outputs[k].value, g.outputs[k].storage}); rest.out_dst.push_back(k); continue; }
+        last.push_back(k);
+        const std::vector<char> cone = cone_of(g, g.outputs[k].value, cuts);
+        for (size_t n = 0; n < cone.size(); n++)
+            if (cone[n] && g.nodes[n].kind == NodeKind::Reduce && (g.nodes[n].axes & ~g.nodes[g.nodes[n].args[0]].bcast & ~unit)) {
+                set_error("a result over an operand that other threads read waits for a reduction");
+                return EWF_EUNSUPPORTED;
+            }
+    }
+    if (!targets.empty()) {
+        rest.exec.reset(new Exec());
+        build_stage(g, targets, false, cuts, *rest.exec, rest.in_src);
+        const ewf_status st = try_stage(rest);
+        if (st != EWF_OK) return st;
+    }
+    std::map<int, int> known = cuts;
+    for (int k : last) {
+        const int v = g.outputs[k].value;
+        const std::vector<char> cone = cone_of(g, v, cuts);
+        bool early = false;
+        for (int j = 0; j < nout; j++) early = early || (j != k && out[j].ptr && reads_from(g, cone, in, out[j].ptr));
+        if (!early || known.count(v)) continue;
+        Stage sg;
+        sg.exec.reset(new Exec());
+        build_stage(g, {{v, g.nodes[v].vtype == EWF_I32 ? EWF_I32 : EWF_F32}}, false, cuts, *sg.exec, sg.in_src);
+        // (a temporary has every axis)
+        for (Node &nd : sg.exec->g.nodes) { nd.in_dropped = 0; nd.keep = true; }
+        plan.temps.push_back(temp_for(g, v, full, ws));
+        sg.out_dst.push_back(-(int)plan.temps.size());
+        const ewf_status st = try_stage(sg);
+        if (st != EWF_OK) return refused(st);
+        known[v] = (int)plan.temps.size() - 1;
+        plan.stages.push_back(std::move(sg));
+    }
+    if (!targets.empty()) plan.stages.push_back(std::move(rest));
+    for (int k : last) {
+        Stage sg;
+        sg.exec.reset(new Exec());
+        build_stage(g, {{g.outputs[k].value, g.outputs[k].storage}}, false, known, *sg.exec, sg.in_src);
+        sg.out_dst.push_back(k);
+        const ewf_status st = try_stage(sg);
+        if (st != EWF_OK) return refused(st);
+        plan.stages.push_back(std::move(sg));
+    }
+    return EWF_OK;
+}
+
+// What every stage inherits from the expression, and its plan for tensors that may be temporaries at
+// stand-in addresses.
+ewf_status plan_stage(const Exec &e, const Graph &g, const int64_t *full, bool strict_rows, const ewf_tensor *in, const ewf_tensor *out,
+                      const Plan &plan, Stage &sg)
+{
+    sg.exec->opts = e.opts;
+    sg.exec->math_flavour = e.math_flavour;
+    sg.exec->auto_math = e.auto_math;
+    sg.exec->is_stage = true;
+    sg.exec->strict_rows = strict_rows;
+    // only an index (iota) makes a stage depend on an axis that none of its inputs spans
+    uint32_t iota_axes = 0;
+    for (const Node &nd : sg.exec->g.nodes) if (nd.kind == NodeKind::Iota) iota_axes |= 1u << nd.index;
+    sg.exec->has_forced_full = iota_axes != 0;
+    for (int d = 0; d < kMaxDims; d++) sg.exec->forced_full[d] = (d < g.ndim && (iota_axes >> d & 1u)) ? full[d] : 1;
+    ewf_status st = finalize_graph(sg.exec->g);
+    if (st != EWF_OK) return st;
+    // tensors of a stage while planning: the caller's, or a temporary at a stand-in address
+    std::vector<ewf_tensor> tin, tout;
+    auto put = [&](std::vector<ewf_tensor> &to, const ewf_tensor *theirs, int s) {
+        if (s >= 0) { to.push_back(theirs[s]); return; }
+        const Temp &t = plan.temps[-s - 1];
+        to.push_back({(void *)(uintptr_t)(kFakeBase + t.offset), t.shape, t.strides});
+    };
+    for (int s : sg.in_src) put(tin, in, s);
+    for (int d : sg.out_dst) put(tout, out, d);
+    Plan *sp = nullptr;
+    st = make_plan(*sg.exec, tin.data(), (int)tin.size(), tout.data(), (int)tout.size(), &sp);
+    if (st != EWF_OK) return st;
+    sg.ws_bytes = sp->workspace_bytes;
+    return EWF_OK;
+}
+
 }  // namespace
 
 ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tensor *in, int nin, const ewf_tensor *out, int nout, Plan &plan)
@@ -101,41 +256,8 @@ ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tenso
     plan.temps.clear();
     std::map<int, int> cuts;                            // node -> temporary
     size_t ws = 0;
-    auto align_up = [](size_t v) { return (v + 255) / 256 * 256; };
-
-    // tensors of a stage while planning: the caller's, or a temporary at a stand-in address
-    auto stage_tensors = [&](const Stage &sg, std::vector<ewf_tensor> &tin, std::vector<ewf_tensor> &tout) {
-        tin.clear(); tout.clear();
-        for (int s : sg.in_src) {
-            if (s >= 0) tin.push_back(in[s]);
-            else { const Temp &t = plan.temps[-s - 1]; tin.push_back({(void *)(uintptr_t)(kFakeBase + t.offset), t.shape, t.strides}); }
-        }
-        for (int d : sg.out_dst) {
-            if (d >= 0) tout.push_back(out[d]);
-            else { const Temp &t = plan.temps[-d - 1]; tout.push_back({(void *)(uintptr_t)(kFakeBase + t.offset), t.shape, t.strides}); }
-        }
-    };
-    auto try_stage = [&](Stage &sg) -> ewf_status {
-        sg.exec->opts = e.opts;
-        sg.exec->math_flavour = e.math_flavour;
-        sg.exec->auto_math = e.auto_math;
-        sg.exec->is_stage = true;
-        sg.exec->strict_rows = strict_rows;
-        // only an index (iota) makes a stage depend on an axis that none of its inputs spans
-        uint32_t iota_axes = 0;
-        for (const Node &nd : sg.exec->g.nodes) if (nd.kind == NodeKind::Iota) iota_axes |= 1u << nd.index;
-        sg.exec->has_forced_full = iota_axes != 0;
-        for (int d = 0; d < kMaxDims; d++) sg.exec->forced_full[d] = (d < g.ndim && (iota_axes >> d & 1u)) ? full[d] : 1;
-        ewf_status s2 = finalize_graph(sg.exec->g);
-        if (s2 != EWF_OK) return s2;
-        std::vector<ewf_tensor> tin, tout;
-        stage_tensors(sg, tin, tout);
-        Plan *sp = nullptr;
-        s2 = make_plan(*sg.exec, tin.data(), (int)tin.size(), tout.data(), (int)tout.size(), &sp);
-        if (s2 != EWF_OK) return s2;
-        sg.ws_bytes = sp->workspace_bytes;
-        return EWF_OK;
-    };
+    const std::vector<int> over = shared_operands(g, unit, in, nin, out, nout);
+    const TryStage try_stage = [&](Stage &sg) { return plan_stage(e, g, full, strict_rows, in, out, plan, sg); };
 
     // Element-wise outputs that an earlier pass can write on its way.  A pass that materialises
     // reductions and already walks the full extents evaluates such an output from the values it
@@ -191,6 +313,11 @@ ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tenso
                 break;
             }
             if (st != EWF_EUNSUPPORTED) return st;
+            if (std::any_of(fin.out_dst.begin(), fin.out_dst.end(), [&](int k) { return over[k] >= 0; })) {
+                st = plan_shared_results(g, fin.out_dst, over, cuts, full, unit, in, out, nout, plan, ws, try_stage);
+                if (st == EWF_OK) break;
+                if (st != EWF_EUNSUPPORTED) return st;
+            }
         }
         // materialise the reductions that depend on no other (unmaterialised) reduction,
         // one stage per set of reduced axes
@@ -248,41 +375,54 @@ ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tenso
             auto attempt = [&](const std::vector<int> &hand, bool group_outputs) -> ewf_status {
                 const size_t ntemps = plan.temps.size(), ws0 = ws;
                 Stage sg;
-                sg.exec.reset(new Exec());
                 std::vector<std::pair<int, ewf_dtype>> targets;
                 for (int n : hand) targets.push_back({n, g.nodes[n].vtype == EWF_I32 ? EWF_I32 : EWF_F32});
-                build_stage(g, targets, true, cuts, *sg.exec, sg.in_src);
                 for (int n : hand) {
-                    Temp t;
-                    t.dtype = g.nodes[n].vtype == EWF_I32 ? EWF_I32 : EWF_F32;
-                    int64_t count = 1;
-                    for (int d = g.ndim - 1; d >= 0; d--) {
-                        t.shape[d] = (g.nodes[n].bcast & (1u << d)) ? 1 : full[d];
-                        t.strides[d] = count;
-                        count *= t.shape[d];
-                    }
-                    t.bytes = (size_t)count * 4;
-                    t.offset = ws;
-                    ws = align_up(ws + t.bytes);
-                    plan.temps.push_back(t);
+                    plan.temps.push_back(temp_for(g, n, full, ws));
                     sg.out_dst.push_back(-(int)plan.temps.size());
                 }
-                std::vector<int> gouts;
-                if (group_outputs)
+                // A result over a shared operand stays out where an output that this stage does not write (with
+                // `riding` it writes those that can ride) reads the operand too.
+                auto group_results = [&](bool riding) {
+                    std::vector<int> here;
+                    if (!group_outputs) return here;
                     for (int k = 0; k < nout; k++) {
                         const int v = g.outputs[k].value;
-                        if (!written[k] && glevel[v] && dep[v] && !g.nodes[v].dropped) gouts.push_back(k);
+                        if (!written[k] && glevel[v] && dep[v] && !g.nodes[v].dropped) here.push_back(k);
                     }
-                if (!gouts.empty()) {
-                    for (int k : gouts) { targets.push_back({g.outputs[k].value, g.outputs[k].storage}); sg.out_dst.push_back(k); }
-                    build_stage(g, targets, true, cuts, *sg.exec, sg.in_src);
-                }
+                    std::vector<char> stop(N, 0);
+                    for (int n : hand) stop[n] = 1;
+                    for (bool changed = true; changed;) {
+                        changed = false;
+                        for (size_t i = 0; i < here.size() && !changed; i++) {
+                            if (over[here[i]] < 0) continue;
+                            for (int j = 0; j < nout && !changed; j++) {
+                                if (written[j] || std::find(here.begin(), here.end(), j) != here.end() || (riding && can_ride(j))) continue;
+                                changed = reads_from(g, cone_of(g, g.outputs[j].value, cuts, &stop), in, out[here[i]].ptr);
+                            }
+                            if (changed) here.erase(here.begin() + i);
+                        }
+                    }
+                    return here;
+                };
+                auto with_outputs = [&](const std::vector<int> &outs, const std::vector<int> &riders) {
+                    Stage s;
+                    s.exec.reset(new Exec());
+                    s.out_dst = sg.out_dst;
+                    std::vector<std::pair<int, ewf_dtype>> all = targets;
+                    for (const std::vector<int> *list : {&outs, &riders})
+                        for (int k : *list) { all.push_back({g.outputs[k].value, g.outputs[k].storage}); s.out_dst.push_back(k); }
+                    build_stage(g, all, true, cuts, *s.exec, s.in_src);
+                    return s;
+                };
+                std::vector<int> gouts = group_results(true);
+                Stage with = with_outputs(gouts, {});
                 // does this pass walk the full extents (then element-wise outputs can ride along)?
                 bool spans_all = true;
                 for (int d = 0; d < g.ndim && spans_all; d++) {
                     if (full[d] <= 1) continue;
                     bool some = false;
-                    for (int node : sg.exec->g.input_node) if (!(sg.exec->g.nodes[node].bcast >> d & 1u)) some = true;
+                    for (int node : with.exec->g.input_node) if (!(with.exec->g.nodes[node].bcast >> d & 1u)) some = true;
                     spans_all = some;
                 }
                 std::vector<int> riders;
@@ -290,13 +430,7 @@ ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tenso
                     for (int k = 0; k < nout; k++) if (can_ride(k)) riders.push_back(k);
                 bool done = false;
                 if (!riders.empty()) {
-                    Stage both;
-                    both.exec.reset(new Exec());
-                    std::vector<std::pair<int, ewf_dtype>> all = targets;
-                    for (int k : riders) all.push_back({g.outputs[k].value, g.outputs[k].storage});
-                    build_stage(g, all, true, cuts, *both.exec, both.in_src);
-                    both.out_dst = sg.out_dst;
-                    for (int k : riders) both.out_dst.push_back(k);
+                    Stage both = with_outputs(gouts, riders);
                     if (try_stage(both) == EWF_OK) {
                         for (int k : riders) written[k] = 1;
                         sg = std::move(both);
@@ -304,6 +438,8 @@ ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tenso
                     }
                 }
                 if (!done) {
+                    gouts = group_results(false);
+                    sg = with_outputs(gouts, {});
                     const ewf_status s3 = try_stage(sg);
                     if (s3 != EWF_OK) { plan.temps.resize(ntemps); ws = ws0; return s3; }
                 }
@@ -356,10 +492,8 @@ ewf_status plan_multi(Exec &e, const Graph &g, bool strict_rows, const ewf_tenso
 ewf_status plan_empty_rest(Exec &e, const int64_t *full, const ewf_tensor *in, int nin, const ewf_tensor *out, int nout,
                            const std::vector<int> &outs, Plan &plan)
 {
-    (void)nin; (void)nout;
     const Graph &g = e.g;
     const int N = (int)g.nodes.size();
-    auto align_up = [](size_t v) { return (v + 255) / 256 * 256; };
     std::vector<char> need(N, 0);
     for (int k : outs) need[g.outputs[k].value] = 1;
     std::map<int, int> cuts;
@@ -379,19 +513,9 @@ ewf_status plan_empty_rest(Exec &e, const int64_t *full, const ewf_tensor *in, i
             set_error("a value is computed from a maximum, minimum or arg-max over an empty axis: only sums (0) and products (1) are defined there");
             return EWF_ESHAPE;
         }
-        Temp t;
-        t.dtype = nd.vtype == EWF_I32 ? EWF_I32 : EWF_F32;
-        int64_t count = 1;
-        for (int d = g.ndim - 1; d >= 0; d--) {
-            t.shape[d] = (nd.bcast >> d & 1u) ? 1 : full[d];
-            t.strides[d] = count;
-            count *= t.shape[d];
-        }
-        if (count <= 0) { set_error("internal: an empty value under an output that is not"); return EWF_ESHAPE; }
-        t.bytes = (size_t)count * 4;
-        t.offset = ws;
-        ws = align_up(ws + t.bytes);
-        plan.temps.push_back(t);
+        plan.temps.push_back(temp_for(g, n, full, ws));
+        const Temp &t = plan.temps.back();
+        if (t.bytes == 0) { set_error("internal: an empty value under an output that is not"); return EWF_ESHAPE; }
         cuts[n] = (int)plan.temps.size() - 1;
         const uint32_t one = t.dtype == EWF_I32 ? 1u : 0x3f800000u;
         plan.temp_fills.push_back({(int)plan.temps.size() - 1, nd.op == EWF_RPROD ? one : 0u});
@@ -401,29 +525,21 @@ ewf_status plan_empty_rest(Exec &e, const int64_t *full, const ewf_tensor *in, i
     std::vector<std::pair<int, ewf_dtype>> targets;
     for (int k : outs) { targets.push_back({g.outputs[k].value, g.outputs[k].storage}); sg.out_dst.push_back(k); }
     build_stage(g, targets, false, cuts, *sg.exec, sg.in_src);
-    sg.exec->opts = e.opts;
-    sg.exec->math_flavour = e.math_flavour;
-    sg.exec->auto_math = e.auto_math;
-    sg.exec->is_stage = true;
-    uint32_t iota_axes = 0;
-    for (const Node &nd : sg.exec->g.nodes) if (nd.kind == NodeKind::Iota) iota_axes |= 1u << nd.index;
-    sg.exec->has_forced_full = iota_axes != 0;
-    for (int d = 0; d < kMaxDims; d++) sg.exec->forced_full[d] = (d < g.ndim && (iota_axes >> d & 1u)) ? full[d] : 1;
-    ewf_status st = finalize_graph(sg.exec->g);
-    if (st != EWF_OK) return st;
-    std::vector<ewf_tensor> tin, tout;
-    for (int s : sg.in_src) {
-        if (s >= 0) tin.push_back(in[s]);
-        else { const Temp &t = plan.temps[-s - 1]; tin.push_back({(void *)(uintptr_t)(kFakeBase + t.offset), t.shape, t.strides}); }
+    const TryStage try_stage = [&](Stage &stage) { return plan_stage(e, g, full, false, in, out, plan, stage); };
+    ewf_status st = try_stage(sg);
+    if (st == EWF_OK) plan.stages.push_back(std::move(sg));
+    else {
+        uint32_t unit = 0;
+        for (int d = 0; d < g.ndim; d++) if (full[d] == 1) unit |= 1u << d;
+        const std::vector<int> over = shared_operands(g, unit, in, nin, out, nout);
+        if (st != EWF_EUNSUPPORTED || std::none_of(outs.begin(), outs.end(), [&](int k) { return over[k] >= 0; })) return st;
+        st = plan_shared_results(g, outs, over, cuts, full, unit, in, out, nout, plan, ws, try_stage);
+        if (st != EWF_OK) return st;
     }
-    for (int d : sg.out_dst) tout.push_back(out[d]);
-    Plan *sp = nullptr;
-    st = make_plan(*sg.exec, tin.data(), (int)tin.size(), tout.data(), (int)tout.size(), &sp);
-    if (st != EWF_OK) return st;
-    sg.ws_bytes = sp->workspace_bytes;
-    sg.ws_offset = ws;
-    ws = align_up(ws + sg.ws_bytes);
-    plan.stages.push_back(std::move(sg));
+    for (Stage &stage : plan.stages) {
+        stage.ws_offset = ws;
+        ws = align_up(ws + stage.ws_bytes);
+    }
     plan.workspace_bytes = ws;
     return EWF_OK;
 }

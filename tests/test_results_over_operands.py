@@ -92,6 +92,102 @@ def test_held_columns_over_an_operand_keep_to_their_columns(rows, cols, storage,
         assert held(_plan(spec, shapes, over)) == (cols % 2 == 0), over
 
 
+def _row(s, n=1): return [s.input("f32", (True, False)) for _ in range(n)]
+
+
+# ---- an operand that several threads read the same element of: (spec, shapes, which results over which operands)
+
+def _beside_elements():
+    s = GraphSpec(2)
+    x, (k,) = s.input("f32", (False, False)), _row(s)
+    s.output(s.add(x, k), "f32")
+    s.output(s.add(k, s.const(2.0)), "f32")
+    return s, [(500, 300), (1, 300)], {1: 1}, ["tile", "tile"]
+
+
+def _exchanged():
+    """Either result reads what the other lies over."""
+    s = GraphSpec(2)
+    x, (a, b) = s.input("f32", (False, False)), _row(s, 2)
+    s.output(s.add(s.add(x, a), b), "f32")
+    s.output(s.add(a, s.mul(b, s.const(2.0))), "f32")
+    s.output(s.sub(b, a), "f16")
+    s.output(s.sub(a, b), "f32")
+    return s, [(301, 700), (1, 700), (1, 700)], {0: 0, 1: 1, 3: 2}, ["tile"] * 5
+
+
+def _running(rows, cols, decay, keep=True):
+    """Normalisation that shifts by the running mean, which is updated; without `decay` the new mean is a value per column
+    that the first pass could write."""
+    s = GraphSpec(2)
+    x, (r,) = s.input("f32", (False, False)), _row(s)
+    mean = s.mul(s.reduce("sum", x, (0,), keep=keep), s.const(1.0 / rows))
+    cen = s.sub(x, mean)
+    top = s.reduce("max", s.apply("abs", cen), (0,), keep=keep)
+    s.output(s.add(s.div(cen, top), r), "f32")
+    s.output(s.add(s.mul(r, s.const(0.75)), s.mul(mean, s.const(0.25))) if decay else s.add(r, mean), "f32")
+    return s, [(rows, cols), (1, cols)], {0: 0, 1: 1}, ["col", "col", "tile", "tile"]
+
+
+def _planes():
+    """Values per channel and place beside sums per channel: they vary along one of the reduced axes."""
+    s = GraphSpec(3)
+    x, k = s.input("f32", (False,) * 3), s.input("f32", (True, False, False))
+    s.output(s.reduce("sum", s.add(x, k), (0, 2)), "f32")
+    s.output(s.mul(k, s.const(0.5)), "f32")
+    return s, [(40, 30, 400), (1, 30, 400)], {1: 1}, None
+
+
+def _empty_batch():
+    s = GraphSpec(3)
+    x, k, r = s.input("f32", (False,) * 3), s.input("f32", (True, False, False)), s.input("f32", (True, True, False))
+    s.output(s.add(s.add(k, s.reduce("sum", x, (0,), keep=True)), r), "f32")
+    s.output(s.add(r, s.reduce("prod", s.reduce("sum", x, (0,), keep=True), (1,), keep=True)), "f32")
+    return s, [(0, 70, 90), (1, 70, 90), (1, 1, 90)], {1: 2}, None
+
+
+SHARED = {"beside elements": _beside_elements, "exchanged": _exchanged, "planes": _planes,
+          "running": lambda: _running(500, 300, True), "running sum": lambda: _running(500, 300, False), "running, dropped axis": lambda: _running(5000, 96, False, False)}
+
+
+@pytest.mark.parametrize("name", sorted(SHARED))
+def test_a_shared_operand_is_overwritten_last(name):
+    spec, shapes, over, want = SHARED[name]()
+    expr = _plan(spec, shapes, over)
+    classes, sources = _kernels(expr)
+    if want: assert classes == want
+    if name == "beside elements": assert expr.workspace == 0          # nothing a caller without one could not run
+    # no launch writes such a result beside another output (the last stages have one output each)
+    shared = sum(shapes[j] != shapes[0] for j in over.values())
+    assert all("out1" not in src for src in sources[-shared:])
+    # apart, the same expressions take no launch more than the results over operands cost
+    assert len(_kernels(_plan(spec, shapes, {}))[0]) < len(classes)
+
+
+def test_results_that_are_written_behind_all_readers_take_no_pass_more():
+    # a bias gradient accumulated beside the gradient that is written over its input; a total over everything
+    s = GraphSpec(2)
+    x, (k,), t = s.input("f32", (False, False)), _row(s), s.input("f32", (True, True))
+    y = s.apply("max", s.add(x, k), s.const(0.0))
+    s.output(y, "f32")
+    s.output(s.add(k, s.reduce("sum", y, (0,), keep=True)), "f32")
+    for over in ({}, {0: 0, 1: 1}):
+        assert _kernels(_plan(s, [(2000, 512), (1, 512), (1, 1)], over))[0] == ["col"]
+    s = GraphSpec(2)
+    x, t = s.input("f32", (False, False)), s.input("f32", (True, True))
+    rows = s.reduce("sum", s.apply("exp", s.sub(x, s.reduce("max", x, (1,), keep=True))), (1,), keep=True)
+    s.output(rows, "f32")
+    s.output(s.add(t, s.reduce("sum", rows, (0,), keep=True)), "f32")
+    for over in ({}, {1: 1}):
+        assert _kernels(_plan(s, [(640, 3000), (1, 1)], over))[0] == ["row"]
+    # an operand that no output reads is only memory
+    s = GraphSpec(2)
+    x, (k, b) = s.input("f32", (False, False)), _row(s, 2)
+    s.output(s.add(x, b), "f32")
+    s.output(s.mul(b, s.const(2.0)), "f32")
+    assert _kernels(_plan(s, [(500, 300), (1, 300), (1, 300)], {1: 1}))[0] == ["tile"]
+
+
 def _picked(rows, cols, total):
     """One element of a row, chosen by an index, beside a result of the row's length."""
     s = GraphSpec(2)
@@ -148,6 +244,19 @@ def _inputs(spec, shapes, rng):
         if storage == "i32": out.append(rng.integers(0, shapes[0][1], shape).astype(np.int32))
         else: out.append(rng.uniform(0.5, 1.5, shape).astype(np.float32))
     return out
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(SHARED) + ["empty batch"])
+def test_results_over_a_shared_operand(name, oracle, G):
+    spec, shapes, over, _ = _empty_batch() if name == "empty batch" else SHARED[name]()
+    host = _inputs(spec, shapes, np.random.default_rng(5))
+    print(f"[case] {name} {shapes}", flush=True)
+    _, got = _run(G, spec, host, over)
+    want = oracle.evaluate(spec, host, nthreads=4)
+    for k, (g, w) in enumerate(zip(got, want)):
+        bar = G.h.HALF if w.dtype == np.float16 else G.h.REDUCTION if name == "planes" and k == 0 else G.h.ELEMENTWISE
+        G.h.compare(f"output {k}", g, w, *bar)
 
 
 @pytest.mark.gpu
