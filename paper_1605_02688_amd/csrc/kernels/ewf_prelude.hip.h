@@ -458,6 +458,18 @@ EWF_DEV T ewf_dpp(const T &v)
     return r;
 }
 
+// The first lane's value in every lane.
+template <typename T>
+EWF_DEV T ewf_first_lane(const T &v)
+{
+    T r;
+    const int *src = reinterpret_cast<const int *>(&v);
+    int *dst = reinterpret_cast<int *>(&r);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); i++) dst[i] = __builtin_amdgcn_readfirstlane(src[i]);
+    return r;
+}
+
 template <typename T>
 EWF_DEV T ewf_lane_xor(const T &v, int mask)
 {
@@ -494,16 +506,20 @@ EWF_DEV T ewf_fold_pairs(F op, const T *smem)
 // ... or one after another.  More than eight meet in pairs: on a chain of sixteen, sums of parts of
 // equal size round twice as far (the sum of 50257 magnitudes per row: relative error 6.7e-8, 4.4e-8 in pairs).
 // Sixteen meet in the same pairs on the lanes of a row: one result per lane is read instead of sixteen, whose
-// registers a row of the row class has not to spare (32 of them for a maximum with its check word).
+// registers a row of the row class has not to spare (32 of them for a maximum with its check word).  Each step takes
+// the lane that lies behind, so the first lane has what the pairs give, and every thread takes that lane's result: on a
+// butterfly, whose operands change places from lane to lane, threads would disagree where the order shows (zeros
+// of either sign, the mean of two groups).
 template <int NWAVES, typename T, typename F>
 EWF_DEV T ewf_fold_waves(F op, const T *smem)
 {
     if constexpr (NWAVES == 16) {
         T v = smem[threadIdx.x & 15];
-        v = op(v, ewf_dpp<0xB1>(v));
-        v = op(v, ewf_dpp<0x4E>(v));
-        v = op(v, ewf_dpp<0x141>(v));
-        return op(v, ewf_dpp<0x140>(v));
+        v = op(v, ewf_dpp<0x101>(v));           // row_shl: lane + 1
+        v = op(v, ewf_dpp<0x102>(v));
+        v = op(v, ewf_dpp<0x104>(v));
+        v = op(v, ewf_dpp<0x108>(v));
+        return ewf_first_lane(v);
     }
     if constexpr (NWAVES > 8) return ewf_fold_pairs<0, NWAVES>(op, smem);
     T r = smem[0];
