@@ -348,8 +348,10 @@ static ewf_status single_kernel_plan(Exec &e, Plan *plan, const int64_t *full)
                 }
                 int widest = 2;
                 for (const Operand &op : c.ops) if (op.stride[c.rank - 1] != 0) widest = std::max(widest, op.storage == EWF_F16 ? 2 : 4);
-                // planes that are no whole number of vectors: one sweep over rows of whole images (gen_flat says which)
-                if (ops_ok && inner < 2048 && outer >= 2 && inner * widest % 16 != 0) {
+                // planes that are no whole number of vectors: one sweep over rows of whole images (gen_flat says which).
+                // Its vectors and its grid are its own, so not under the options that set either.
+                const bool shaped = e.opts.force_scalar || e.opts.max_blocks > 0 || e.opts.tile_elems > 0;
+                if (ops_ok && !shaped && inner < 2048 && outer >= 2 && inner * widest % 16 != 0) {
                     plan->kclass = KernelClass::Col;
                     plan->flat_strips = true;
                     planned = generate(e, *plan) == EWF_OK;

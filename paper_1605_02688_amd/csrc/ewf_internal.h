@@ -215,7 +215,7 @@ struct Plan {
     size_t workspace_bytes = 0;
     bool empty = false;                  // zero-size iteration space: nothing to traverse
     // The kernel was generated for vectors wider than the layout's alignment allows (canon.vec_loose at
-    // most; canon.vec says how wide, except for the lane class, whose plan keeps the strict width):
+    // most; canon.vec says how wide, except for the lane and column classes, whose plans keep the strict width):
     // rows may start at any element and end inside a vector.  Whole vectors are read and written with
     // accesses that assume element alignment only, the last vector of a row moved into place.
     bool loose_vec = false;

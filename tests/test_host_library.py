@@ -1001,3 +1001,29 @@ def test_tiles_of_the_stress_expression(reading, shape, tile):
     n, c, h, w = shape
     e = plan_workload(wl.layout_only(wl.c5_stress, n=n, c=c, h=h, w=w, reading=reading))[0]
     assert e.info()["kernel_class"] == "tile" and e.info()["staged_operands"] == 1 and int(np.prod(e.info()["tile"])) == tile, e.info()
+
+
+@pytest.mark.parametrize("kind", ["sums", "backward"])
+@pytest.mark.parametrize("option", [{}, {"force_scalar": 1}, {"max_blocks": 3}, {"tile_elems": 512}, {"block_threads": 512}, {"unroll": 3}])
+def test_sums_over_ragged_planes_keep_to_the_options(kind, option):
+    s = GraphSpec(3)
+    x, b = s.input("f32", (False,) * 3), s.input("f32", (True, False, True))
+    y = s.apply("max", s.add(x, b), s.const(0.0))
+    if kind == "backward": s.output(y, "f32")
+    s.output(s.reduce("sum", y, (0, 2)), "f32")
+    s.output(s.reduce("max", y, (0, 2)), "f32")
+    expr = ewf.Expression(s, **option)
+    ins = [ref(BASE, (64, 300, 49)), ref(BASE + (1 << 32), (1, 300, 1))]
+    outs = [ref(BASE + (2 + k << 32), shape) for k, shape in enumerate(expr.output_shapes(ins))]
+    expr.plan(ins, outs)
+    info = expr.info()
+    multi = info["kernel_class"] == "multi"
+    sources = [ewf.debug_source(expr.handle, k) for k in range(info["grid_blocks"])] if multi else [expr.source()]
+    infos = [ewf.debug_plan_info(expr.handle, k) for k in range(info["grid_blocks"])] if multi else [info]
+    # whole vectors at any alignment and a grid of its own, unless the call says what either may be
+    flat = not {"force_scalar", "max_blocks", "tile_elems"} & set(option)
+    assert any("sm_flat" in src for src in sources) == flat
+    if "force_scalar" in option: assert all("#define EWF_VEC 1\n" in src for src in sources)
+    if "max_blocks" in option: assert all(i["grid_blocks"] <= 3 for i in infos)
+    if "block_threads" in option: assert infos[0]["block_threads"] == 512
+    if "unroll" in option: assert "u < 3" in sources[0]
