@@ -1,6 +1,6 @@
 """GPU parity of chained reductions down columns that a workgroup holds whole in its registers: one launch for the
 statistics and the normalised tensor.  Strips whose last vector is cut, a last strip narrower than a vector, a last step that
-some threads have no row for, operands read for the outputs only, results written over the input."""
+some threads have no row for, operands read for the outputs only, results written over either operand."""
 import numpy as np
 import pytest
 
@@ -58,3 +58,14 @@ def test_normalisation_of_held_columns(rows, cols, storage, oracle, G):
     e2.run([xd, yd, gd], outs, (), ws, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     G.h.compare("in place", outs[0].cpu().numpy(), want[0], *(G.h.ELEMENTWISE if storage == "f32" else G.h.HALF))
+    # (vectors that the last column cuts belong to two threads: such calls take passes)
+    assert e2.info()["kernel_class"] == ("multi" if cols % 2 else "col"), e2.info()
+    # over the operand that each row's outputs read just before they are written
+    xd = torch.from_numpy(x).cuda()
+    e3 = G.ewf.Expression(spec)
+    outs = [yd] + outs[1:]
+    ws = G.h.make_workspace(e3, [xd, yd, gd], outs)
+    e3.run([xd, yd, gd], outs, (), ws, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert e3.info()["kernel_class"] == ("multi" if cols % 2 else "col"), e3.info()
+    G.h.compare("over the other operand", outs[0].cpu().numpy(), want[0], *(G.h.ELEMENTWISE if storage == "f32" else G.h.HALF))

@@ -1,6 +1,6 @@
 """GPU parity of long rows whose vectors start on the output's cache lines: every remainder of a row's length, rows
 aligned to a vector but not to a line, a float32 result of float16 rows, input and output of different pitches, rows of
-NaN next to others, a result written over the input."""
+NaN next to others, a result written over the input, workgroups that take several rows in turn."""
 import numpy as np
 import pytest
 
@@ -26,6 +26,16 @@ CASES += [("f32", "f32", 2600, 5003, 7), ("f16", "f16", 5100, 5003, 5), ("f16", 
 
 @pytest.mark.parametrize("storage,out,rows,cols,gap", CASES)
 def test_rows_that_start_inside_a_line(storage, out, rows, cols, gap, oracle, G):
+    _check(storage, out, rows, cols, gap, oracle, G)
+
+
+# more than 8192 rows, or a grid of fewer workgroups than rows: a workgroup's rows start at different distances from a line
+@pytest.mark.parametrize("storage,rows,cols,opts", [("f16", 10000, 5003, {}), ("f32", 8193, 5001, {}), ("f32", 2600, 5003, {"max_blocks": 301}), ("f16", 5100, 5005, {"max_blocks": 64})])
+def test_rows_in_turn(storage, rows, cols, opts, oracle, G):
+    _check(storage, storage, rows, cols, 0, oracle, G, **opts)
+
+
+def _check(storage, out, rows, cols, gap, oracle, G, **opts):
     torch = G.torch
     dt = np.float16 if storage == "f16" else np.float32
     rng = np.random.default_rng(cols + gap)
@@ -38,7 +48,7 @@ def test_rows_that_start_inside_a_line(storage, out, rows, cols, gap, oracle, G)
     spec = _spec(storage, out)
     print(f"[case] {storage} to {out} {rows} x {cols} pitch {cols + gap}", flush=True)
     xd = torch.from_numpy(buf).cuda()[:, gap // 2:gap // 2 + cols]
-    expr = G.ewf.Expression(spec)
+    expr = G.ewf.Expression(spec, **opts)
     outs = G.h.alloc_outputs(expr, spec, [xd])
     guard = torch.full((rows * cols + 64,), 7.0, dtype=outs[0].dtype, device="cuda")        # what lies behind the last row stays
     outs[0] = guard[:rows * cols].view(rows, cols)
@@ -47,6 +57,7 @@ def test_rows_that_start_inside_a_line(storage, out, rows, cols, gap, oracle, G)
     expr.run([xd], outs, (), ws, stream)
     torch.cuda.synchronize()
     assert expr.info()["kernel_class"] == "row" and "head_" in expr.source(), expr.info()
+    assert ("row += gridDim.x" in expr.source()) == (rows > 8192 or "max_blocks" in opts)
     assert (guard[rows * cols:] == 7.0).all()
     pick = list(range(70)) + [rows - 2, rows - 1]                # every distance of a row's start from a line
     want = oracle.evaluate(spec, [np.ascontiguousarray(x[pick])], nthreads=8)
@@ -55,7 +66,7 @@ def test_rows_that_start_inside_a_line(storage, out, rows, cols, gap, oracle, G)
     G.h.compare("total", got[1][pick], want[1], *G.h.REDUCTION)
     if storage == out:                                           # over the input
         outs2 = [xd, outs[1]]
-        e2 = G.ewf.Expression(spec)
+        e2 = G.ewf.Expression(spec, **opts)
         e2.run([xd], outs2, (), G.h.make_workspace(e2, [xd], outs2), stream)
         torch.cuda.synchronize()
         if gap == 0: np.testing.assert_array_equal(xd.cpu().numpy(), got[0])
