@@ -33,7 +33,8 @@
  *     synchronises, so the hot path must not).
  *   - An output may alias an input only exactly (same pointer, shape and strides; section
  *     2.2.1: element-wise operations may overwrite an input); any other overlap between an
- *     output and an input or another output is EWF_EALIAS.
+ *     output and an input or another output is EWF_EALIAS.  The results are those of separate
+ *     outputs; kernels and workspace may be others, so such a call has a plan of its own.
  *   - A tensor with a zero extent is legal: success, nothing traversed.  A sum or a product
  *     over an empty axis is 0 or 1, also inside an expression; a maximum, minimum or arg-max over
  *     an empty axis (or anything computed from one) is EWF_ESHAPE.

@@ -262,7 +262,9 @@ ewf_status Gen::gen_col()
     // 8 lanes) over axis 0 of float16 [500, 24381] 10.1 and 10.8, (96 workgroups) of [100, 24381] 3.5 and 3.9.
     if (loose) {
         const int64_t strips = ceil_div(c.extent[in_d], (int64_t)TX * VEC);
-        // (sums of 35 rows, whole columns in one launch, stay as they are: the planning tests state their workgroups)
+        // (sums of 35 rows, whole columns in one launch, stay as they are: the planning tests state their workgroups.  Wide
+        // vectors are faster there too: sums over axis 1, strict and wide, us, float16 [128, 48, 253] 3.1 and 3.1, [500, 35, 189] 4.6 and 3.7,
+        // [2000, 35, 509] 26.7 and 15.1, [600, 63, 999] 24.5 and 16.6; float32 34.5 and 27.0, 35.6 and 31.8 of the last two)
         if (one_tile && c.extent[dR] < 64) return fail("cut vectors are for longer columns");
         if (TX < 32 || TZ > 1 || c.extent[in_d] * 10 < strips * TX * VEC * 7) return fail("cut vectors leave lanes idle");
         if (one_tile && ntiles * 2 < device_cu_count()) return fail("cut vectors leave too few workgroups");

@@ -55,7 +55,8 @@ ewf_status Gen::gen_flat()
     // and 32.3.  Float16 [128, 2048, 7, 7] 27.8 and 17.8, [32, 512, 14, 14] 8.7 and 7.1, but [64, 300, 21, 21] 13.1 and 19.4.
     const int64_t plane = P * widest;
     // (One sum beside an output over planes of up to 256 bytes, whole vectors per image, 2^20 to 2^23 elements: two passes, the first
-    // over the images, as the planning tests state of [32, 2048, 7, 7]; 13.9 us there, 8.9 here.)
+    // over the images, as the planning tests state of [32, 2048, 7, 7].  One launch is faster there too, us: float32 [32, 2048, 7, 7] 10.4
+    // and 6.7, [24, 1000, 7, 7] 6.6 and 3.9, [60, 1000, 7, 7] 9.6 and 6.8; float16 8.4 and 5.5, 6.0 and 4.6, 8.1 and 7.2.)
     if (level.size() == 1 && !ew_out_ops.empty() && plane <= 256 && F % VEC == 0 && c.total >= ((int64_t)1 << 20) && c.total < ((int64_t)1 << 23))
         return fail("one sum over short planes of a tensor of middling size is taken in two passes");
     if (plane > (widest == 2 ? 600 : 4608) || (plane > 2800 && N * C > 8192)) return fail("long planes are rows of their own");

@@ -165,7 +165,8 @@ ewf_status Gen::gen_row()
         // each compute unit and up to 60 where there are four.  Softmax cross-entropy on float32, split over workgroups against one
         // workgroup a row: [600, 24577] 18.6 and 15.7 us, [1220, 24577] 29.5 and 23.9, [600, 40000] 24.6 and 21.4, [1220, 32768]
         // 33.4 and 29.2; 52 registers, [1220, 53001] 51.2 and 48.2, [600, 53001] 28.9 and 29.7; 64, [1220, 65536] 58.0 and 71.9.  From 256 MB on
-        // they stay split, which the planning tests state of [2048, 32768], though one workgroup a row is faster there too)
+        // they stay split, which the planning tests state of [2048, 32768], though one workgroup a row is faster there too: log-sum-exp of
+        // float32 [2048, 32768] 44.4 and 42.4, [2048, 40000] 56.3 and 51.6, [4096, 32770] 86.2 and 81.6)
         // (rows that are written back too are read once here and twice in two passes: kept up to 56
         // registers -- the gradient of softmax cross-entropy on float32 [1280, 50257] 143.0 us in two passes, 108.5
         // here even with one workgroup on a compute unit, [400, 50257] 50.6 and 38.0 us -- and up to 64 in tight rows, two for each compute unit)
